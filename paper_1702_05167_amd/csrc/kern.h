@@ -256,29 +256,43 @@ int dd_inv_nb(int max_n);
 // columns of a super-panel of the double-double Gauss-Jordan (its pivot rows update the rest at once)
 constexpr int kDDSuper = 64;
 
-// ---- double-double products from 8-bit slices on the integer matrix cores (ozaki.hip) ----
-// slices per operand: S = 16 (the default) keeps each double-double operand to 2^-112 of its row's
-// (or column's) largest entry, S = 15 to 2^-105
+// ---- double-double products from int8 residues on the integer matrix cores (ozaki.hip) ----
+// S = 16 (the default) keeps each double-double operand to 2^-112 of its row's (or column's)
+// largest entry, S = 15 to 2^-105 (7 S bits)
 constexpr int kOzSlices = 16;
 constexpr int kOzSlicesMin = 15, kOzSlicesMax = 16;
-// deepest slice product: the int32 accumulator of one weight sums up to 3 Gauss parts x S pairs x
-// 64^2 x Kp, which must stay below 2^31
+constexpr int kOzPlanes = 64;   // residue planes of an operand, one byte per element each
+// deepest product: 10880 with S = 16, 11648 with S = 15 (the residues' range allows 17147)
 constexpr int oz_max_depth(int slices) { return (int)(((1ll << 31) - 1) / (3ll * slices * 64 * 64) / 64 * 64); }
+constexpr int oz_rows(int n) { return (n + 31) / 32 * 32; }   // rows of an operand's planes
 // One operand to split: element (r, k) = X[r * ldr + k * ldk] for r < R, k < K (complex
-// double-double); out = 3 x S planes (Re, Im, Re + Im) of Rp x Kp int8 in 1 KB fragments of
-// 16 rows x 64 k (matrix-core operand order), ex = [Rp] row exponents; Rp a multiple of 32 (>= R),
-// Kp of 64 (>= K); zero padding.  Row-scale workgroups [blk_off, blk_off + ceil(Rp / 64)) and digit
-// workgroups [tile_off, tile_off + ceil(Rp / 64) * Kp / 32) of a split launch belong to this job.
+// double-double); out = kOzPlanes planes of Rp x Kp int8 in 1 KB fragments of 16 rows x 64 k
+// (matrix-core operand order), ex = [Rp] row exponents; Rp a multiple of 32 (>= R), Kp of 64 (>= K);
+// zero padding.  Workgroups [tile_off, tile_off + oz_split_blocks(Rp, Kp, kper)) of a split launch belong to
+// this job: a row block of 16 and kper steps of 64 k each.
 struct OzSplitJob {
   const zdd* X;
   int64_t ldr, ldk;
   int32_t R, K, Rp, Kp;
   int8_t* out;
   int32_t* ex;
-  int32_t blk_off, tile_off;
+  int32_t tile_off, kper;
 };
+constexpr int oz_split_blocks(int Rp, int Kp, int kper) {
+  const int chunks = (Kp / 64 + kper - 1) / kper;
+  return Rp / 16 * (chunks > 0 ? chunks : 1);
+}
+// 64-k steps per workgroup of a split launch of row_blocks row blocks: all of them once the launch fills
+// the chip (a workgroup reads its rows twice, for the scale and for the residues), fewer to bring a
+// small launch to some 1024 workgroups
+constexpr int oz_split_steps(int row_blocks, int Kp) {
+  const int kcs = Kp / 64 > 0 ? Kp / 64 : 1;
+  int chunks = row_blocks > 0 ? 1024 / row_blocks : 1;
+  chunks = chunks < 1 ? 1 : chunks > kcs ? kcs : chunks;
+  return (kcs + chunks - 1) / chunks;
+}
 // One product D = (-1)^negate A' B' + beta C from split operands (A8: rows of A', B8: columns of
-// B'); 32 x 32 output tiles.
+// B'); 64 x 32 output tiles.
 struct GemmProbOZ {
   const int8_t* A8;
   const int8_t* B8;
@@ -292,13 +306,14 @@ struct GemmProbOZ {
   int32_t tiles_n, tile_off;
 };
 // slices: kOzSlicesMin..kOzSlicesMax, the same for the split and the product of one operand pair
-void launch_oz_split(hipStream_t st, int slices, const OzSplitJob* jobs, const int32_t* blk_job, int total_blocks,
-                     const int32_t* tile_job, int total_tiles);
+void launch_oz_split(hipStream_t st, int slices, const OzSplitJob* jobs, const int32_t* tile_job, int total_tiles);
 void launch_oz_gemm(hipStream_t st, int slices, const GemmProbOZ* probs, const int32_t* tile_prob, int total_tiles,
                     int negate, int beta);
-// the allocation-free product: a static device array of kOzNoAllocScratch bytes per device holds
-// descriptors, maps, slices and exponents of one problem (oz_noalloc_bytes of them)
-constexpr size_t kOzNoAllocScratch = size_t(64) << 20;
+// the allocation-free product: a static device array per device holds descriptors, maps, residues
+// and exponents of one problem.  Products are accepted up to kOzNoAllocLimit by oz_noalloc_bytes
+// (48 B per element of the padded operands); the residues take 64 B, at most 4/3 of that limit.
+constexpr size_t kOzNoAllocLimit = size_t(64) << 20;
+constexpr size_t kOzNoAllocScratch = size_t(86) << 20;
 void* oz_noalloc_scratch_address();
 size_t oz_noalloc_bytes(int M, int N, int K);
 int launch_oz_gemm_noalloc(hipStream_t st, char* ws, int opA, int opB, int M, int N, int K, int negate,

@@ -630,12 +630,13 @@ struct Builder {
   static constexpr int kOzMinK = 32;
   static constexpr size_t kOzStepCap = size_t(4) << 30;   // slice scratch of one product step
   // Measured costs on the target (seconds): splitting one complex double-double element into
-  // slices, one padded multiply-add of the slice product, one multiply-add on the vector units.
-  static constexpr double kOzSplitCost = 25e-12, kOzMacCost = 0.55e-12, kValuMacCost = 1.5e-12;
+  // residues, one padded multiply-add and one output of the residue product, one multiply-add on the
+  // vector units.
+  static constexpr double kOzSplitCost = 25e-12, kOzMacCost = 0.1e-12, kOzOutCost = 12e-12, kValuMacCost = 1.5e-12;
   bool oz_pays(const GPD& g) const {
     if (g.K < kOzMinK || g.K > oz_max_depth(slices)) return false;
-    const double Mp = oz_round(g.M, 32), Np = oz_round(g.N, 32), Kp = oz_round(g.K, 64);
-    const double t_oz = kOzSplitCost * ((g.sa ? 0.0 : Mp) + Np) * Kp + kOzMacCost * Mp * Np * Kp;
+    const double Mp = oz_rows(g.M), Np = oz_rows(g.N), Kp = oz_round(g.K, 64);
+    const double t_oz = kOzSplitCost * ((g.sa ? 0.0 : Mp) + Np) * Kp + (kOzMacCost * Kp + kOzOutCost) * Mp * Np;
     return t_oz < kValuMacCost * (double)g.M * g.N * g.K;
   }
   void dd_gemm(int opA, int opB, const std::vector<GPD>& ps, int negate, int beta) {
@@ -648,7 +649,7 @@ struct Builder {
 
   static size_t oz_round(size_t v, size_t a) { return (v + a - 1) / a * a; }
   size_t oz_bytes(int R, int K) const {
-    return oz_round((size_t)3 * slices * oz_round(R, 32) * oz_round(K, 64) + 4 * oz_round(R, 32), 256);
+    return oz_round((size_t)kOzPlanes * oz_rows(R) * oz_round(K, 64) + 4 * (size_t)oz_rows(R), 256);
   }
 
   // split + product steps, the problem list cut into pieces whose slices fit kOzStepCap; an operand
@@ -657,7 +658,7 @@ struct Builder {
     size_t i0 = 0;
     while (i0 < ps.size()) {
       std::vector<OzSplitJob> sj;
-      std::vector<int32_t> bmap, tmap_s;
+      std::vector<int32_t> tmap_s;
       std::vector<GemmProbOZ> gp;
       std::vector<int32_t> tmap;
       std::map<std::tuple<const void*, int64_t, int64_t, int, int>, std::pair<size_t, size_t>> seen;
@@ -670,11 +671,11 @@ struct Builder {
         const auto key = std::make_tuple((const void*)X, ldr, ldk, R, K);
         auto it = seen.find(key);
         if (it != seen.end()) return it->second;
-        const int Rp = (int)oz_round(R, 32), Kp = (int)oz_round(K, 64);
+        const int Rp = oz_rows(R), Kp = (int)oz_round(K, 64);
         size_t off;
         if (keep) {
           off = reinterpret_cast<size_t>(wsbase + keep);
-          const auto r = std::make_pair(off, off + (size_t)3 * slices * Rp * Kp);
+          const auto r = std::make_pair(off, off + (size_t)kOzPlanes * Rp * Kp);
           seen[key] = r;
           if (std::find(oz_kept.begin(), oz_kept.end(), keep) != oz_kept.end()) return r;
           oz_kept.push_back(keep);
@@ -685,15 +686,10 @@ struct Builder {
         OzSplitJob j{};
         j.X = X; j.ldr = ldr; j.ldk = ldk; j.R = R; j.K = K; j.Rp = Rp; j.Kp = Kp;
         j.out = reinterpret_cast<int8_t*>(off);
-        j.ex = reinterpret_cast<int32_t*>(off + (size_t)3 * slices * Rp * Kp);
+        j.ex = reinterpret_cast<int32_t*>(off + (size_t)kOzPlanes * Rp * Kp);
         kept_job.push_back(keep ? 1 : 0);
-        const int rblocks = (Rp + 63) / 64;
-        j.blk_off = (int32_t)bmap.size();
-        for (int b = 0; b < rblocks; ++b) bmap.push_back((int32_t)sj.size());
-        j.tile_off = (int32_t)tmap_s.size();
-        for (int b = 0; b < rblocks * (Kp / 32); ++b) tmap_s.push_back((int32_t)sj.size());
         sj.push_back(j);
-        const auto r = std::make_pair(off, off + (size_t)3 * slices * Rp * Kp);
+        const auto r = std::make_pair(off, off + (size_t)kOzPlanes * Rp * Kp);
         seen[key] = r;
         return r;
       };
@@ -713,21 +709,28 @@ struct Builder {
         p.eb = reinterpret_cast<const int32_t*>(b.second);
         p.C = g.C; p.D = g.D; p.D64 = g.D64;
         p.M = g.M; p.N = g.N;
-        p.Mp = (int)oz_round(g.M, 32); p.Np = (int)oz_round(g.N, 32); p.Kp = (int)oz_round(g.K, 64);
+        p.Mp = oz_rows(g.M); p.Np = oz_rows(g.N); p.Kp = (int)oz_round(g.K, 64);
         p.ldc = g.ldc; p.ldd = g.ldd; p.ldd64 = g.ldd64;
         p.tiles_n = p.Np / 32;
         p.tile_off = (int32_t)tmap.size();
-        const int tiles = (p.Mp / 32) * p.tiles_n;
+        const int tiles = (p.Mp + 63) / 64 * p.tiles_n;
         for (int k = 0; k < tiles; ++k) tmap.push_back((int32_t)gp.size());
         gp.push_back(p);
         flops += 8.0 * g.M * g.N * g.K;
-        // slices of op(A) and op(B) (3 parts x S slices of one byte per complex element), their
-        // scales, the double-double result (and its rounded copy), C when accumulating
-        bytes += 3.0 * slices * ((double)g.M * g.K + (double)g.K * g.N) + 4.0 * (g.M + g.N) +
+        // residues of op(A) and op(B) (kOzPlanes bytes per complex element), their scales, the
+        // double-double result (and its rounded copy), C when accumulating
+        bytes += kOzPlanes * ((double)g.M * g.K + (double)g.K * g.N) + 4.0 * (g.M + g.N) +
                  (double)g.M * g.N * (32.0 + (g.D64 ? 16.0 : 0.0) + (beta ? 32.0 : 0.0));
       }
       oz_need = std::max(oz_need, cur);
       if (!sj.empty()) {
+        int row_blocks = 0;
+        for (const OzSplitJob& j : sj) row_blocks += j.Rp / 16;
+        for (size_t q = 0; q < sj.size(); ++q) {
+          sj[q].kper = oz_split_steps(row_blocks, sj[q].Kp);
+          sj[q].tile_off = (int32_t)tmap_s.size();
+          tmap_s.insert(tmap_s.end(), oz_split_blocks(sj[q].Rp, sj[q].Kp, sj[q].kper), (int32_t)q);
+        }
         Step s;
         s.kind = S_OZ_SPLIT;
         s.jobs = blob.push(sj);
@@ -736,10 +739,8 @@ struct Builder {
           blob.sc_relocs.push_back(s.jobs + q * sizeof(OzSplitJob) + offsetof(OzSplitJob, out));
           blob.sc_relocs.push_back(s.jobs + q * sizeof(OzSplitJob) + offsetof(OzSplitJob, ex));
         }
-        s.map = blob.push(bmap);
-        s.count = (int)bmap.size();
-        s.map_k[0] = blob.push(tmap_s);
-        s.count_k[0] = (int)tmap_s.size();
+        s.map = blob.push(tmap_s);
+        s.count = (int)tmap_s.size();
         push(s);
       }
       if (!gp.empty()) {
@@ -1605,8 +1606,7 @@ int run_steps(hsc_ctx* ctx, hipStream_t st, Plan* pl, int e_base, int nvalid, vo
                        reinterpret_cast<const int32_t*>(pl->blob + s.map_k[s.tile]), s.count_k[s.tile], s.i1, s.beta);
         break;
       case S_OZ_SPLIT:
-        launch_oz_split(st, pl->slices, (const OzSplitJob*)jobs, map, s.count,
-                        reinterpret_cast<const int32_t*>(pl->blob + s.map_k[0]), s.count_k[0]);
+        launch_oz_split(st, pl->slices, (const OzSplitJob*)jobs, map, s.count);
         break;
       case S_OZ_GEMM:
         launch_oz_gemm(st, pl->slices, (const GemmProbOZ*)jobs, map, s.count, s.i1, s.beta);
@@ -2661,13 +2661,13 @@ size_t oz_pad(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // one product on the integer matrix cores (split A', split B', slice product), synchronous
 hsc_status kern_zgemm_oz(hsc_ctx* ctx, int slices, int opA, int opB, int M, int N, int K, int negate, const void* A,
                          int lda, const void* B, int ldb, int beta, const void* C, int ldc, void* D, int ldd) {
-  const int Mp = (int)oz_pad(M, 32), Np = (int)oz_pad(N, 32), Kp = (int)oz_pad(K, 64);
-  const size_t sa = (size_t)3 * slices * Mp * Kp, sb = (size_t)3 * slices * Np * Kp;
-  const int ba = (Mp + 63) / 64, bb = (Np + 63) / 64;
-  const int ta = ba * (Kp / 32), tb = bb * (Kp / 32);
-  const int tiles = (Mp / 32) * (Np / 32);
-  // layout: [jobs: A, B split; product][maps: scale blocks, digit tiles, product tiles][A8][B8][ea][eb]
-  const size_t nmap = (size_t)(ba + bb) + (size_t)(ta + tb) + (size_t)tiles;
+  const int Mp = oz_rows(M), Np = oz_rows(N), Kp = (int)oz_pad(K, 64);
+  const size_t sa = (size_t)kOzPlanes * Mp * Kp, sb = (size_t)kOzPlanes * Np * Kp;
+  const int kper = oz_split_steps((Mp + Np) / 16, Kp);
+  const int ta = oz_split_blocks(Mp, Kp, kper), tb = oz_split_blocks(Np, Kp, kper);
+  const int tiles = (Mp + 63) / 64 * (Np / 32);
+  // layout: [jobs: A, B split; product][maps: split workgroups, product tiles][A8][B8][ea][eb]
+  const size_t nmap = (size_t)(ta + tb) + (size_t)tiles;
   const size_t o_map = 1024, o_a8 = oz_pad(o_map + 4 * nmap, 256);
   const size_t o_b8 = oz_pad(o_a8 + sa, 256), o_ea = oz_pad(o_b8 + sb, 256), o_eb = oz_pad(o_ea + 4 * (size_t)Mp, 256);
   const size_t bytes = o_eb + 4 * (size_t)Np;
@@ -2679,11 +2679,11 @@ hsc_status kern_zgemm_oz(hsc_ctx* ctx, int slices, int opA, int opB, int M, int 
   ja.X = (const zdd*)A; ja.R = M; ja.K = K; ja.Rp = Mp; ja.Kp = Kp;
   if (opA == 0) { ja.ldr = lda; ja.ldk = 1; } else { ja.ldr = 1; ja.ldk = lda; }
   ja.out = (int8_t*)(dev + o_a8); ja.ex = (int32_t*)(dev + o_ea);
-  ja.blk_off = 0; ja.tile_off = 0;
+  ja.tile_off = 0; ja.kper = kper;
   jb.X = (const zdd*)B; jb.R = N; jb.K = K; jb.Rp = Np; jb.Kp = Kp;
   if (opB == 0) { jb.ldr = 1; jb.ldk = ldb; } else { jb.ldr = ldb; jb.ldk = 1; }
   jb.out = (int8_t*)(dev + o_b8); jb.ex = (int32_t*)(dev + o_eb);
-  jb.blk_off = ba; jb.tile_off = ta;
+  jb.tile_off = ta; jb.kper = kper;
   GemmProbOZ p{};
   p.A8 = ja.out; p.B8 = jb.out; p.ea = ja.ex; p.eb = jb.ex;
   p.C = (const zdd*)C; p.D = (zdd*)D; p.D64 = nullptr;
@@ -2693,14 +2693,13 @@ hsc_status kern_zgemm_oz(hsc_ctx* ctx, int slices, int opA, int opB, int M, int 
   std::memcpy(host.data(), job, sizeof(job));
   std::memcpy(host.data() + 512, &p, sizeof(p));
   int32_t* m = reinterpret_cast<int32_t*>(host.data() + o_map);
-  for (int b = 0; b < ba + bb; ++b) m[b] = b < ba ? 0 : 1;                        // scale blocks
-  for (int b = 0; b < ta + tb; ++b) m[ba + bb + b] = b < ta ? 0 : 1;              // digit tiles
+  for (int b = 0; b < ta + tb; ++b) m[b] = b < ta ? 0 : 1;   // split workgroups
   // product tiles: all 0 (one problem)
   hipError_t e = hipMemcpy(dev, host.data(), host.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) {
     const int32_t* dm = (const int32_t*)(dev + o_map);
-    launch_oz_split(ctx->stream, slices, (const OzSplitJob*)dev, dm, ba + bb, dm + ba + bb, ta + tb);
-    launch_oz_gemm(ctx->stream, slices, (const GemmProbOZ*)(dev + 512), dm + ba + bb + ta + tb, tiles, negate, beta);
+    launch_oz_split(ctx->stream, slices, (const OzSplitJob*)dev, dm, ta + tb);
+    launch_oz_gemm(ctx->stream, slices, (const GemmProbOZ*)(dev + 512), dm + ta + tb, tiles, negate, beta);
     e = hipGetLastError();
     if (e == hipSuccess) e = ctx->stream ? hipStreamSynchronize(ctx->stream) : hipDeviceSynchronize();
   }
@@ -2830,9 +2829,9 @@ hsc_status hsc_kern_zgemm_dd_noalloc(hsc_ctx* ctx, int32_t opA, int32_t opB, int
   }
   if (M == 0 || N == 0) return HSC_OK;
   const size_t need = oz_noalloc_bytes(M, N, K);
-  if (need > kOzNoAllocScratch) {
+  if (need > kOzNoAllocLimit) {
     set_error("hsc_kern_zgemm_dd_noalloc: the product needs " + std::to_string(need) + " bytes of scratch, more than the " +
-              std::to_string(kOzNoAllocScratch) + " of the static device array");
+              std::to_string(kOzNoAllocLimit) + " of the static device array");
     return HSC_E_ARG;
   }
   if (!ctx->noalloc) {
