@@ -66,18 +66,6 @@ __device__ __forceinline__ dd dd_mul(dd x, dd y) {
 
 __device__ __forceinline__ dd dd_from(double a) { return dd{a, 0.0}; }
 
-// x / y: two Newton corrections of the FP64 quotient
-__device__ __forceinline__ dd dd_div(dd x, dd y) {
-#pragma clang fp contract(off)
-  const double q1 = x.hi / y.hi;
-  dd r = dd_sub(x, dd_mul(dd_from(q1), y));
-  const double q2 = r.hi / y.hi;
-  r = dd_sub(r, dd_mul(dd_from(q2), y));
-  const double q3 = r.hi / y.hi;
-  dd q = quick_two_sum(q1, q2);
-  return dd_add(q, dd_from(q3));
-}
-
 __device__ __forceinline__ zdd zdd_from(double2 v) { return zdd{dd{v.x, 0.0}, dd{v.y, 0.0}}; }
 __device__ __forceinline__ double2 zdd_round(zdd v) { return make_double2(v.re.hi + v.re.lo, v.im.hi + v.im.lo); }
 __device__ __forceinline__ zdd zdd_zero() { return zdd{dd{0.0, 0.0}, dd{0.0, 0.0}}; }
@@ -92,15 +80,25 @@ __device__ __forceinline__ zdd zdd_mul(zdd a, zdd b) {
 // acc + a * b
 __device__ __forceinline__ zdd zdd_fma(zdd acc, zdd a, zdd b) { return zdd_add(acc, zdd_mul(a, b)); }
 
-// 1 / a = conj(a) / |a|^2, with the larger component scaled out
+// 1 / d for d in [1, 8]: the FP64 reciprocal and one Newton step with the exact residual
+__device__ __forceinline__ dd dd_rcp(dd d) {
+#pragma clang fp contract(off)
+  double y = __builtin_amdgcn_rcp(d.hi);
+  y = fma(y, fma(-d.hi, y, 1.0), y);
+  y = fma(y, fma(-d.hi, y, 1.0), y);
+  const double r = fma(-d.lo, y, fma(-d.hi, y, 1.0));
+  return quick_two_sum(y, y * r);
+}
+
+// 1 / a = conj(a) / |a|^2, scaled by the power of two of the larger component (0 for a = 0)
 __device__ __forceinline__ zdd zdd_rcp(zdd a) {
   const double s = fmax(fabs(a.re.hi), fabs(a.im.hi));
   if (s == 0.0) return zdd_zero();
-  const dd inv_s = dd_from(1.0 / s);   // exact only up to rounding; it cancels below
-  const dd ar = dd_mul(a.re, inv_s), ai = dd_mul(a.im, inv_s);
-  const dd den = dd_add(dd_mul(ar, ar), dd_mul(ai, ai));   // |a/s|^2
-  const dd qr = dd_div(ar, den), qi = dd_div(dd_neg(ai), den);
-  return zdd{dd_mul(qr, inv_s), dd_mul(qi, inv_s)};
+  const int e = -ilogb(s);
+  const dd ar{ldexp(a.re.hi, e), ldexp(a.re.lo, e)}, ai{ldexp(a.im.hi, e), ldexp(a.im.lo, e)};
+  const dd q = dd_rcp(dd_add(dd_mul(ar, ar), dd_mul(ai, ai)));   // 1 / |a 2^e|^2, |a 2^e|^2 in [1, 8)
+  const dd re = dd_mul(ar, q), im = dd_mul(dd_neg(ai), q);
+  return zdd{dd{ldexp(re.hi, e), ldexp(re.lo, e)}, dd{ldexp(im.hi, e), ldexp(im.lo, e)}};
 }
 
 // Lazy accumulation of a sum of double-double products (the GEMM inner loop): hi

@@ -75,152 +75,138 @@ __global__ __launch_bounds__(RB) void k_dd_assemble(const RowJob* __restrict__ j
 }
 
 // ---------------------------------------------------------------------------------------------
-// Gauss-Jordan panel in double-double (same algorithm as k_inv_panel)
+// Gauss-Jordan in double-double with partial pivoting inside the block and no row interchanges: the pivot
+// row p_k of column k stays where it is (piv[k] = p_k, mark[p_k] = 1), later columns choose among the
+// unmarked rows, and the inverse comes out permuted: X[p_j][k] = (A^-1)[j][p_k].
 constexpr int PT = 512;
 
-template <int RPT, int NB>
-__global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_dd_inv_panel(
-    const InvJobDD* __restrict__ jobs, int k0, int nbw, int32_t* __restrict__ status) {
+// largest of 64 lanes, in scalar registers
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+#define HSC_DPP_MAX(ctrl) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, false))
+  HSC_DPP_MAX(0x111);   // row_shr 1, 2, 4, 8: lane 15 of every 16 has the row's largest
+  HSC_DPP_MAX(0x112);
+  HSC_DPP_MAX(0x114);
+  HSC_DPP_MAX(0x118);
+  HSC_DPP_MAX(0x142);   // row_bcast 15, 31: lane 63 has the wave's
+  HSC_DPP_MAX(0x143);
+#undef HSC_DPP_MAX
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// One panel of NB columns from k0, one workgroup per matrix, each thread RPT rows.  A serial chain of NB
+// column steps: pivot search, reciprocal, update of the panel.  The pivot is the row with the largest
+// leading 8 mantissa bits (and exponent) of |Re| + |Im|, the first of equals: one 32-bit key per row, one
+// maximum.  Every thread forms the reciprocal itself (no round trip through LDS), and the columns
+// rotate through the registers so that the step's code is a loop body (the current column is P[.][0]).
+// Also written: T = the panel's columns minus the identity at the pivots, R = the pivot rows' old values in
+// the other columns of the super-panel [s0, s1) (zero in the panel's own), the factors of its update.
+template <int TH, int RPT, int NB>
+__global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_dd_inv_panel(
+    const InvJobDD* __restrict__ jobs, int k0, int s0, int sw, int32_t* __restrict__ status) {
   const InvJobDD jb = jobs[blockIdx.x];
   const int n = jb.n;
   if (k0 >= n) return;
-  const int nb = min(nbw, n - k0);
+  const int nb = min(NB, n - k0);
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  __shared__ double red_v[PT / 64];
-  __shared__ int red_i[PT / 64];
-  __shared__ zdd rowp[NB], rowc[NB], srow[NB];
-  __shared__ int bad;
-  if (t == 0) bad = 0;
+  __shared__ uint32_t red[2][TH / 64];
+  __shared__ zdd rowp[2][NB];
+  __shared__ int prows[NB];
+  bool bad = false;
 
   zdd P[RPT][NB];
+  bool open[RPT];   // not a pivot row yet
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {
-    const int r = t + q * PT;
+    const int r = t + q * TH;
+    open[q] = r < n && (k0 == 0 || jb.mark[r] == 0);
 #pragma unroll
     for (int j = 0; j < NB; ++j) P[q][j] = (r < n && j < nb) ? jb.X[(int64_t)r * jb.ld + k0 + j] : zdd_zero();
   }
-  __syncthreads();
-
+#pragma unroll 1
+  for (int j = 0; j < nb; ++j) {
+    const int par = j & 1;
+    uint32_t key = 0;
 #pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    if (j < nb) {
-      const int c = k0 + j;
-      double bv = -1.0;
-      int bi = n;
-#pragma unroll
-      for (int q = 0; q < RPT; ++q) {
-        const int r = t + q * PT;
-        if (r >= c && r < n) {
-          const double v = zdd_cabs1(P[q][j]);
-          if (v > bv) { bv = v; bi = r; }
-        }
+    for (int q = 0; q < RPT; ++q)
+      if (open[q]) {
+        const uint32_t v = (uint32_t)__double2hiint(zdd_cabs1(P[q][0]));
+        key = max(key, (v & 0xfffff000u) | (uint32_t)(4095 - (t + q * TH)));
       }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        const double ov = __shfl_xor(bv, off, 64);
-        const int oi = __shfl_xor(bi, off, 64);
-        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-      }
-      if (lane == 0) { red_v[w] = bv; red_i[w] = bi; }
+    key = wave_max_u32(key);
+    if (TH > 64) {
+      if (lane == 0) red[par][w] = key;
       __syncthreads();
-      double pv = red_v[0];
-      int prow = red_i[0];
+      key = red[par][0];
 #pragma unroll
-      for (int k = 1; k < PT / 64; ++k) {
-        const double ov = red_v[k];
-        const int oi = red_i[k];
-        if (ov > pv || (ov == pv && oi < prow)) { pv = ov; prow = oi; }
+      for (int i = 1; i < TH / 64; ++i) key = max(key, red[par][i]);
+    }
+    const int prow = 4095 - (int)(key & 4095u);
+#pragma unroll
+    for (int q = 0; q < RPT; ++q)
+      if (t + q * TH == prow) {
+#pragma unroll
+        for (int jj = 0; jj < NB; ++jj) rowp[par][jj] = P[q][jj];
       }
-      if (prow >= n) { prow = c; pv = 0.0; }
+    __syncthreads();
+    const zdd pivv = rowp[par][0];
+    const zdd inv = zdd_rcp(pivv);
+    bad = bad || !(zdd_cabs1(pivv) > 0.0) || !isfinite(pivv.re.hi) || !isfinite(pivv.im.hi);
+    if (t == 0) prows[j] = prow;
+    zdd g[RPT];
 #pragma unroll
-      for (int q = 0; q < RPT; ++q) {
-        const int r = t + q * PT;
-        if (r == prow) {
+    for (int q = 0; q < RPT; ++q) {
+      g[q] = zdd_neg(zdd_mul(P[q][0], inv));
+      if (t + q * TH == prow) {   // the pivot row becomes inv times itself
+        g[q] = inv;
+        open[q] = false;
 #pragma unroll
-          for (int jj = 0; jj < NB; ++jj) rowp[jj] = P[q][jj];
-        }
-        if (r == c && prow != c) {
-#pragma unroll
-          for (int jj = 0; jj < NB; ++jj) rowc[jj] = P[q][jj];
-        }
-      }
-      if (t == 0) jb.piv[c] = prow;
-      __syncthreads();
-      if (t < NB) {
-        const zdd pivv = rowp[j];
-        const zdd inv = zdd_rcp(pivv);
-        srow[t] = (t == j) ? inv : zdd_mul(rowp[t], inv);
-        if (t == 0 && (!(pv > 0.0) || !isfinite(pivv.re.hi) || !isfinite(pivv.im.hi))) bad = 1;
-      }
-      __syncthreads();
-      const zdd inv = srow[j];
-#pragma unroll
-      for (int q = 0; q < RPT; ++q) {
-        const int r = t + q * PT;
-        if (r == c) {
-#pragma unroll
-          for (int jj = 0; jj < NB; ++jj) P[q][jj] = srow[jj];
-        } else {
-          if (r == prow) {
-#pragma unroll
-            for (int jj = 0; jj < NB; ++jj) P[q][jj] = rowc[jj];
-          }
-          const zdd m = P[q][j];
-#pragma unroll
-          for (int jj = 0; jj < NB; ++jj)
-            if (jj != j) P[q][jj] = zdd_sub(P[q][jj], zdd_mul(m, srow[jj]));
-          P[q][j] = zdd_neg(zdd_mul(m, inv));
-        }
+        for (int jj = 1; jj < NB; ++jj) P[q][jj] = zdd_zero();
       }
     }
+#pragma unroll
+    for (int jj = 1; jj < NB; ++jj) {
+      const zdd b = rowp[par][jj];
+#pragma unroll
+      for (int q = 0; q < RPT; ++q) {
+        zddacc a{{P[q][jj].re.hi, P[q][jj].re.lo}, {P[q][jj].im.hi, P[q][jj].im.lo}};
+        zddacc_fma(a, g[q], b);
+        P[q][jj - 1] = zddacc_value(a);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) P[q][NB - 1] = g[q];
   }
+  // after nb rotations P[q][i] holds column (i + nb) mod NB of the panel
+  __syncthreads();
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {
-    const int r = t + q * PT;
+    const int r = t + q * TH;
     if (r < n) {
+      jb.mark[r] = open[q] ? 0 : 1;
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
+      for (int i = 0; i < NB; ++i) {
+        const int j = i + nb < NB ? i + nb : i + nb - NB;
         if (j < nb) {
-          jb.X[(int64_t)r * jb.ld + k0 + j] = P[q][j];
-          zdd v = P[q][j];
-          if (r == k0 + j) v.re = dd_add(v.re, dd_from(-1.0));
+          zdd v = P[q][i];
+          jb.X[(int64_t)r * jb.ld + k0 + j] = v;
+          if (r == prows[j]) v.re = dd_add(v.re, dd_from(-1.0));
           jb.T[(int64_t)r * nb + j] = v;
         }
       }
     }
   }
-  __syncthreads();
+  if (t < nb) jb.piv[k0 + t] = prows[t];
+  const int ws = min(s0 + sw, n) - s0;
+  for (int i = t; i < nb * ws; i += TH) {
+    const int j = i / ws, c = s0 + i % ws;
+    jb.R[(int64_t)j * n + c] = (c >= k0 && c < k0 + nb) ? zdd_zero() : jb.X[(int64_t)prows[j] * jb.ld + c];
+  }
   if (t == 0 && bad && status) atomicMin(&status[jb.e], (int32_t)HSC_E_SINGULAR);
 }
 
-__global__ __launch_bounds__(256) void k_dd_inv_swap(const InvJobDD* __restrict__ jobs, int k0, int nbw,
-                                                     int chunks) {
-  const InvJobDD jb = jobs[blockIdx.x / chunks];
-  const int n = jb.n;
-  if (k0 >= n) return;
-  const int nb = min(nbw, n - k0);
-  const int col = (blockIdx.x % chunks) * 256 + threadIdx.x;
-  if (col >= n) return;
-  const bool in_panel = col >= k0 && col < k0 + nb;
-  if (!in_panel) {
-    for (int j = 0; j < nb; ++j) {
-      const int c = k0 + j, p = jb.piv[c];
-      if (p != c) {
-        zdd* a = jb.X + (int64_t)c * jb.ld + col;
-        zdd* b = jb.X + (int64_t)p * jb.ld + col;
-        const zdd x = *a;
-        *a = *b;
-        *b = x;
-      }
-    }
-  }
-  for (int j = 0; j < nb; ++j)
-    jb.R[(int64_t)j * n + col] = in_panel ? zdd_zero() : jb.X[(int64_t)(k0 + j) * jb.ld + col];
-}
-
-// After the panels of a super-panel [s0, s0 + ws) (two-level Gauss-Jordan, as inverse.hip):
-//   U[r][c] = X[r][s0 + c] - (r == s0 + c)   (n x ws, row stride W; the T workspace)
-//   R[c][j] = X[s0 + c][j]                     (ws x n; the R workspace)
+// After the panels of a super-panel [s0, s0 + ws):
+//   U[r][c] = X[r][s0 + c] - (r == p_(s0 + c))   (n x ws, row stride W; the T workspace)
+//   R[c][j] = X[p_(s0 + c)][j]                     (ws x n; the R workspace)
 __global__ __launch_bounds__(64) void k_dd_inv_super_u(const InvJobDD* __restrict__ jobs, int s0, int W, int chunks) {
   const InvJobDD jb = jobs[blockIdx.x / chunks];
   const int n = jb.n;
@@ -229,9 +215,10 @@ __global__ __launch_bounds__(64) void k_dd_inv_super_u(const InvJobDD* __restric
   const int c = threadIdx.x;
   const int r0 = (blockIdx.x % chunks) * 16;
   if (c >= ws) return;
+  const int p = jb.piv[s0 + c];
   for (int r = r0; r < min(n, r0 + 16); ++r) {
     zdd v = jb.X[(int64_t)r * jb.ld + s0 + c];
-    if (r == s0 + c) v.re = dd_add(v.re, dd_from(-1.0));
+    if (r == p) v.re = dd_add(v.re, dd_from(-1.0));
     jb.T[(int64_t)r * W + c] = v;
   }
 }
@@ -245,9 +232,10 @@ __global__ __launch_bounds__(256) void k_dd_inv_super_r(const InvJobDD* __restri
   const int c = rem / chunks;
   const int j = (rem % chunks) * 256 + threadIdx.x;
   if (c >= ws || j >= n) return;
-  jb.R[(int64_t)c * n + j] = jb.X[(int64_t)(s0 + c) * jb.ld + j];
+  jb.R[(int64_t)c * n + j] = jb.X[(int64_t)jb.piv[s0 + c] * jb.ld + j];
 }
 
+// Y[j][p_k] = X[p_j][k], with its rounded copy
 __global__ __launch_bounds__(256) void k_dd_inv_unscramble(const InvJobDD* __restrict__ jobs, int rows_per_block,
                                                            int chunks) {
   extern __shared__ int idx[];
@@ -255,36 +243,29 @@ __global__ __launch_bounds__(256) void k_dd_inv_unscramble(const InvJobDD* __res
   const int n = jb.n;
   const int r0 = (blockIdx.x % chunks) * rows_per_block;
   if (r0 >= n) return;
-  for (int j = threadIdx.x; j < n; j += blockDim.x) idx[j] = j;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int c = n - 1; c >= 0; --c) {
-      const int p = jb.piv[c];
-      const int a = idx[c];
-      idx[c] = idx[p];
-      idx[p] = a;
-    }
-  }
+  for (int k = threadIdx.x; k < n; k += blockDim.x) idx[jb.piv[k]] = k;
   __syncthreads();
   const int r1 = min(n, r0 + rows_per_block);
-  for (int r = r0; r < r1; ++r)
+  for (int r = r0; r < r1; ++r) {
+    const int64_t src = (int64_t)jb.piv[r] * jb.ld;
     for (int j = threadIdx.x; j < n; j += blockDim.x) {
-      const zdd v = jb.X[(int64_t)r * jb.ld + idx[j]];
+      const zdd v = jb.X[src + idx[j]];
       jb.Y[(int64_t)r * jb.ldy + j] = v;
       jb.Y64[(int64_t)r * jb.ldy64 + j] = zdd_round(v);
     }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
 // grouped complex double-double GEMM: 256 threads as 16 x 16, each with an RM x RN block of outputs
-// (tile BM x BN = 16 RM x 16 RN: 32x32, 64x32 or 64x64), three real products per complex
+// (tile BM x BN = 16 RM x 16 RN: 32x32, 64x32, 64x64 or 16x16), three real products per complex
 // multiply-add (Gauss; the sums re + im of both operands are formed once, when a tile is staged),
 // lazily accumulated (dd.h: ddacc) and renormalised after every 8-deep k step.
 //   OPA 0: A'(m,k) = A[m*lda + k];  OPA 1: A'(m,k) = A[k*lda + m]
 //   OPB 0: B'(k,n) = B[k*ldb + n];  OPB 1: B'(k,n) = B[n*ldb + k]
 constexpr int DK = 8;
-constexpr int kDDConfigs = 3;
-constexpr int kDDRM[kDDConfigs] = {2, 4, 4}, kDDRN[kDDConfigs] = {2, 2, 4};
+constexpr int kDDConfigs = 4;
+constexpr int kDDRM[kDDConfigs] = {2, 4, 4, 1}, kDDRN[kDDConfigs] = {2, 2, 4, 1};
 
 template <int OPA, int OPB, int RM, int RN>
 __global__ __launch_bounds__(256) void k_dd_gemm(const GemmProbDD* __restrict__ probs,
@@ -312,10 +293,11 @@ __global__ __launch_bounds__(256) void k_dd_gemm(const GemmProbDD* __restrict__ 
 #pragma unroll
     for (int j = 0; j < RN; ++j) t1[i][j] = t2[i][j] = t3[i][j] = ddacc{0.0, 0.0};
   for (int k0 = 0; k0 < K; k0 += DK) {
-    // stage A' (BM x DK) and B' (DK x BN), RM / 2 and RN / 2 elements per thread
+    // stage A' (BM x DK) and B' (DK x BN); the 16 x 16 tile takes half the threads for each
 #pragma unroll
-    for (int u = 0; u < RM / 2; ++u) {
+    for (int u = 0; u < (RM + 1) / 2; ++u) {
       const int idx = t + u * 256;
+      if (RM == 1 && idx >= BM * DK) break;
       const int mm = OPA == 0 ? idx / DK : idx % BM;
       const int kk = OPA == 0 ? idx % DK : idx / BM;
       const int gm = m0 + mm, gk = k0 + kk;
@@ -325,8 +307,9 @@ __global__ __launch_bounds__(256) void k_dd_gemm(const GemmProbDD* __restrict__ 
       Ass[kk][mm] = dd_add(v.re, v.im);
     }
 #pragma unroll
-    for (int u = 0; u < RN / 2; ++u) {
-      const int idx = t + u * 256;
+    for (int u = 0; u < (RN + 1) / 2; ++u) {
+      const int idx = RN == 1 ? t - BM * DK : t + u * 256;
+      if (RN == 1 && idx < 0) break;
       const int bk = OPB == 0 ? idx / BN : idx % DK;
       const int bn = OPB == 0 ? idx % BN : idx / DK;
       const int gbk = k0 + bk, gbn = n0 + bn;
@@ -509,6 +492,7 @@ void launch_dd_gemm(hipStream_t st, int opA, int opB, int config, const GemmProb
   if (total_tiles <= 0) return;
   if (config == 1) dd_gemm_dispatch<4, 2>(st, opA, opB, probs, tile_prob, total_tiles, negate, beta);
   else if (config == 2) dd_gemm_dispatch<4, 4>(st, opA, opB, probs, tile_prob, total_tiles, negate, beta);
+  else if (config == 3) dd_gemm_dispatch<1, 1>(st, opA, opB, probs, tile_prob, total_tiles, negate, beta);
   else dd_gemm_dispatch<2, 2>(st, opA, opB, probs, tile_prob, total_tiles, negate, beta);
 }
 
@@ -548,20 +532,18 @@ void launch_dd_assemble(hipStream_t st, const RowJob* jobs, const int32_t* row_j
   hipLaunchKernelGGL(k_dd_assemble, dim3(total_rows), dim3(RB), 0, st, jobs, row_job, es);
 }
 
-void launch_dd_inv_panel(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int nb, int max_n,
+void launch_dd_inv_panel(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int s0, int sw, int max_n,
                          int32_t* status) {
   if (njobs <= 0 || max_n > 8 * PT) return;
-  dim3 g(njobs), b(PT);
-  if (max_n <= 512) hipLaunchKernelGGL((k_dd_inv_panel<1, 8>), g, b, 0, st, jobs, k0, nb, status);
-  else if (max_n <= 1024) hipLaunchKernelGGL((k_dd_inv_panel<2, 8>), g, b, 0, st, jobs, k0, nb, status);
-  else if (max_n <= 2048) hipLaunchKernelGGL((k_dd_inv_panel<4, 4>), g, b, 0, st, jobs, k0, nb, status);
-  else hipLaunchKernelGGL((k_dd_inv_panel<8, 2>), g, b, 0, st, jobs, k0, nb, status);
-}
-
-void launch_dd_inv_swap(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int nb, int max_n) {
-  if (njobs <= 0) return;
-  const int chunks = (max_n + 255) / 256;
-  hipLaunchKernelGGL(k_dd_inv_swap, dim3(njobs * chunks), dim3(256), 0, st, jobs, k0, nb, chunks);
+  const dim3 g(njobs);
+  // as few waves as hold the rows: they share the CU's vector units
+  if (max_n <= 64) hipLaunchKernelGGL((k_dd_inv_panel<64, 1, 8>), g, dim3(64), 0, st, jobs, k0, s0, sw, status);
+  else if (max_n <= 128) hipLaunchKernelGGL((k_dd_inv_panel<128, 1, 8>), g, dim3(128), 0, st, jobs, k0, s0, sw, status);
+  else if (max_n <= 256) hipLaunchKernelGGL((k_dd_inv_panel<256, 1, 8>), g, dim3(256), 0, st, jobs, k0, s0, sw, status);
+  else if (max_n <= 512) hipLaunchKernelGGL((k_dd_inv_panel<512, 1, 8>), g, dim3(512), 0, st, jobs, k0, s0, sw, status);
+  else if (max_n <= 1024) hipLaunchKernelGGL((k_dd_inv_panel<512, 2, 8>), g, dim3(512), 0, st, jobs, k0, s0, sw, status);
+  else if (max_n <= 2048) hipLaunchKernelGGL((k_dd_inv_panel<512, 4, 4>), g, dim3(512), 0, st, jobs, k0, s0, sw, status);
+  else hipLaunchKernelGGL((k_dd_inv_panel<512, 8, 2>), g, dim3(512), 0, st, jobs, k0, s0, sw, status);
 }
 
 void launch_dd_inv_super(hipStream_t st, const InvJobDD* jobs, int njobs, int s0, int W, int max_n) {

@@ -214,7 +214,8 @@ struct InvJobDD {
   double2* Y64;
   int32_t n, ld, ldy, ldy64;
   int32_t e;
-  int32_t* piv;
+  int32_t* piv;    // [n] pivot row of each column
+  int32_t* mark;   // [n] 1 for the pivot rows chosen so far
   zdd* T;
   zdd* R;
 };
@@ -230,7 +231,9 @@ struct GemmProbDD {
   int32_t tiles_n;
   int32_t tile_off;
 };
-// tile configurations of the double-double GEMM: 0 = 32x32, 1 = 64x32, 2 = 64x64 (rows x columns)
+// tile configurations of the double-double GEMM: 0 = 32x32, 1 = 64x32, 2 = 64x64, 3 = 16x16 (rows x
+// columns); the first kDDPublicConfigs are selectable through hsc_kern_zgemm_dd
+constexpr int kDDPublicConfigs = 3;
 int dd_gemm_configs();
 int dd_gemm_tile_m(int config);
 int dd_gemm_tile_n(int config);
@@ -246,9 +249,10 @@ void launch_dd_diag(hipStream_t st, const RowJob* jobs, const int32_t* row_job, 
 // frontal assembly in double-double (RowJob.dst and ChildRef.U point to zdd)
 void launch_dd_assemble(hipStream_t st, const RowJob* jobs, const int32_t* row_job, int total_rows,
                         const EnergyScalars* es);
-void launch_dd_inv_panel(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int nb, int max_n,
+// the panel of dd_inv_nb(max_n) columns from k0 inside the super-panel [s0, s0 + sw): factored in place,
+// with T and R the factors of the update of the super-panel's other columns
+void launch_dd_inv_panel(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int s0, int sw, int max_n,
                          int32_t* status);
-void launch_dd_inv_swap(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int nb, int max_n);
 void launch_dd_inv_unscramble(hipStream_t st, const InvJobDD* jobs, int njobs, int max_n);
 // two-level Gauss-Jordan: T = super-panel columns minus identity (row stride W), R = its pivot rows
 void launch_dd_inv_super(hipStream_t st, const InvJobDD* jobs, int njobs, int s0, int W, int max_n);

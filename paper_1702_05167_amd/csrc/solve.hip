@@ -297,7 +297,7 @@ struct Builder {
       for (int e = 0; e < B; ++e) {
         CS& s = cs[(size_t)i * B + e];
         s.Inv = wsa(n * n * 16);
-        s.piv = wsa(n * 4);
+        s.piv = wsa(2 * n * 4);   // pivots and, double-double, the marks of their rows
         if (ddf) {
           s.Invd = wsa(n * n * 32);
           if (!root(i)) s.Psid = wsa(n * f * 32);
@@ -816,10 +816,9 @@ struct Builder {
     const int SW = kDDSuper;
     for (int s0 = 0; s0 < maxn; s0 += SW) {
       for (int k0 = s0; k0 < std::min(s0 + SW, maxn); k0 += nb) {
-        Step p; p.kind = S_DD_INV_PANEL; p.jobs = ijo; p.njobs = (int)ij.size(); p.i0 = k0; p.i1 = nb; p.i2 = maxn;
+        Step p; p.kind = S_DD_INV_PANEL; p.jobs = ijo; p.njobs = (int)ij.size(); p.i0 = k0; p.i1 = s0; p.i2 = maxn;
         push(p);
-        Step w = p; w.kind = S_DD_INV_SWAP;
-        push(w);
+        if (maxn <= nb) continue;   // no other columns
         std::vector<GPD> ps;
         for (const InvJobDD& j : ij) {
           if (k0 >= j.n) continue;
@@ -890,6 +889,7 @@ struct Builder {
           j.Y64 = W(s.Inv); j.ldy64 = n_of(i);
           j.n = n_of(i); j.e = e;
           j.piv = reinterpret_cast<int32_t*>(wsbase + s.piv);
+          j.mark = j.piv + n_of(i);
           j.T = Z(s.Td); j.R = Z(s.Rd);
           ij.push_back(j);
         }
@@ -1495,8 +1495,14 @@ hsc_status fold_events(hsc_ctx* ctx) {
   return HSC_OK;
 }
 
-// double-double GEMM tile configuration of an untuned plan (64x32)
-constexpr int kDefaultDDConfig = 1;
+// double-double GEMM tile configuration of an untuned step: a thread's time per k step grows with its
+// block of outputs, so the largest tile that still gives every CU two workgroups (64x32 outside
+// the smallest launches)
+int default_dd_config(const Step& s) {
+  for (int c : {1, 0})
+    if (s.count_k[c] >= 512) return c;
+  return 3;
+}
 
 // tile size used by a launch kind of launch_gemm
 int tile_dims_of(int kind) {
@@ -1517,7 +1523,7 @@ const int kKinds3[] = {4, 5, 7, 8};
 bool step_empty(const Step& s) {
   switch (s.kind) {
     case S_INV_PANEL: case S_INV_SWAP: case S_INV_UNSCR: case S_INV_SUPER: case S_GUARD:
-    case S_DD_INV_PANEL: case S_DD_INV_SWAP: case S_DD_INV_UNSCR: case S_DD_INV_SUPER:
+    case S_DD_INV_PANEL: case S_DD_INV_UNSCR: case S_DD_INV_SUPER:
     case S_FACE_HALF: case S_FACE_SIGMA:
       return s.njobs <= 0;
     case S_BONDS:
@@ -1590,10 +1596,7 @@ int run_steps(hsc_ctx* ctx, hipStream_t st, Plan* pl, int e_base, int nvalid, vo
         launch_dd_assemble(st, (const RowJob*)jobs, map, s.count, pl->es);
         break;
       case S_DD_INV_PANEL:
-        launch_dd_inv_panel(st, (const InvJobDD*)jobs, s.njobs, s.i0, s.i1, s.i2, pl->status);
-        break;
-      case S_DD_INV_SWAP:
-        launch_dd_inv_swap(st, (const InvJobDD*)jobs, s.njobs, s.i0, s.i1, s.i2);
+        launch_dd_inv_panel(st, (const InvJobDD*)jobs, s.njobs, s.i0, s.i1, kDDSuper, s.i2, pl->status);
         break;
       case S_DD_INV_UNSCR:
         launch_dd_inv_unscramble(st, (const InvJobDD*)jobs, s.njobs, s.i2);
@@ -1740,7 +1743,7 @@ hsc_status upload_plan(Builder& b, Plan* pl) {
   pl->steps = std::move(b.steps);
   for (Step& s : pl->steps) {
     if (s.kind == S_GEMM) s.tile = pl->m3 ? 4 : 0;   // default kernels: 64x64 tiles, 16x16x4 MFMA
-    if (s.kind == S_DD_GEMM) s.tile = kDefaultDDConfig;
+    if (s.kind == S_DD_GEMM) s.tile = default_dd_config(s);
   }
   return HSC_OK;
 }
@@ -2769,9 +2772,9 @@ hsc_status hsc_kern_zgemm_dd(hsc_ctx* ctx, int32_t config, int32_t opA, int32_t 
                              int32_t K, int32_t negate, const void* A, int32_t lda, const void* B, int32_t ldb,
                              int32_t beta, const void* C, int32_t ldc, void* D, int32_t ldd) {
   // configs past the vector-unit tiles: the slice product with 16 slices (3) or 15 (4)
-  const int oz_slices = config == dd_gemm_configs() ? 16 : config == dd_gemm_configs() + 1 ? 15 : 0;
+  const int oz_slices = config == kDDPublicConfigs ? 16 : config == kDDPublicConfigs + 1 ? 15 : 0;
   if (!ctx || M < 0 || N < 0 || K < 0 || opA < 0 || opA > 1 || opB < 0 || opB > 1 || (beta != 0 && beta != 1) ||
-      (negate != 0 && negate != 1) || config < 0 || config > dd_gemm_configs() + 1 ||
+      (negate != 0 && negate != 1) || config < 0 || config > kDDPublicConfigs + 1 ||
       (oz_slices && K > oz_max_depth(oz_slices))) {
     set_error("bad arguments to hsc_kern_zgemm_dd");
     return HSC_E_ARG;
@@ -2858,7 +2861,7 @@ hsc_status hsc_kern_zinv_dd(hsc_ctx* ctx, int32_t n, void* X, int32_t ld, void* 
   const size_t W = std::max<size_t>(dd_inv_nb(n), kDDSuper);
   size_t ws = 0;
   auto wa = [&](size_t b) { size_t o = (ws + 255) / 256 * 256; ws = o + b; return o; };
-  const size_t o_piv = wa(sizeof(int32_t) * n), o_t = wa(32 * W * n), o_r = wa(32 * W * n);
+  const size_t o_piv = wa(2 * sizeof(int32_t) * n), o_t = wa(32 * W * n), o_r = wa(32 * W * n);
   const size_t o_st = wa(sizeof(int32_t));
   const size_t o_y64 = wa(16ull * n * n);   // the unscramble step always writes the rounded inverse too
   Plan pl;
@@ -2877,7 +2880,7 @@ hsc_status hsc_kern_zinv_dd(hsc_ctx* ctx, int32_t n, void* X, int32_t ld, void* 
   InvJobDD j{};
   j.X = (zdd*)X; j.ld = ld; j.Y = (zdd*)Y; j.ldy = ldy; j.Y64 = (double2*)(pl.ws + o_y64); j.ldy64 = n; j.n = n;
   j.e = 0;
-  j.piv = (int32_t*)(pl.ws + o_piv); j.T = (zdd*)(pl.ws + o_t); j.R = (zdd*)(pl.ws + o_r);
+  j.piv = (int32_t*)(pl.ws + o_piv); j.mark = j.piv + n; j.T = (zdd*)(pl.ws + o_t); j.R = (zdd*)(pl.ws + o_r);
   b.dd_inverse(std::vector<InvJobDD>{j}, n);
   hsc_status rc = upload_plan(b, &pl);
   if (rc != HSC_OK) return rc;
