@@ -204,29 +204,29 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void
   if (t == 0 && bad && status) atomicMin(&status[jb.e], (int32_t)HSC_E_SINGULAR);
 }
 
-// After the panels of a super-panel [s0, s0 + ws):
+// After the panels of the columns [s0, s0 + ws), ws <= W, of a matrix with other columns to update:
 //   U[r][c] = X[r][s0 + c] - (r == p_(s0 + c))   (n x ws, row stride W; the T workspace)
 //   R[c][j] = X[p_(s0 + c)][j]                     (ws x n; the R workspace)
 __global__ __launch_bounds__(64) void k_dd_inv_super_u(const InvJobDD* __restrict__ jobs, int s0, int W, int chunks) {
   const InvJobDD jb = jobs[blockIdx.x / chunks];
   const int n = jb.n;
-  if (s0 >= n) return;
+  if (s0 >= n || n <= (W == kDDSuper ? W : kDDBlockMin)) return;
   const int ws = min(W, n - s0);
-  const int c = threadIdx.x;
   const int r0 = (blockIdx.x % chunks) * 16;
-  if (c >= ws) return;
-  const int p = jb.piv[s0 + c];
-  for (int r = r0; r < min(n, r0 + 16); ++r) {
-    zdd v = jb.X[(int64_t)r * jb.ld + s0 + c];
-    if (r == p) v.re = dd_add(v.re, dd_from(-1.0));
-    jb.T[(int64_t)r * W + c] = v;
+  for (int c = threadIdx.x; c < ws; c += 64) {
+    const int p = jb.piv[s0 + c];
+    for (int r = r0; r < min(n, r0 + 16); ++r) {
+      zdd v = jb.X[(int64_t)r * jb.ld + s0 + c];
+      if (r == p) v.re = dd_add(v.re, dd_from(-1.0));
+      jb.T[(int64_t)r * W + c] = v;
+    }
   }
 }
 
 __global__ __launch_bounds__(256) void k_dd_inv_super_r(const InvJobDD* __restrict__ jobs, int s0, int W, int chunks) {
   const InvJobDD jb = jobs[blockIdx.x / (W * chunks)];
   const int n = jb.n;
-  if (s0 >= n) return;
+  if (s0 >= n || n <= (W == kDDSuper ? W : kDDBlockMin)) return;
   const int ws = min(W, n - s0);
   const int rem = blockIdx.x % (W * chunks);
   const int c = rem / chunks;
@@ -547,7 +547,7 @@ void launch_dd_inv_panel(hipStream_t st, const InvJobDD* jobs, int njobs, int k0
 }
 
 void launch_dd_inv_super(hipStream_t st, const InvJobDD* jobs, int njobs, int s0, int W, int max_n) {
-  if (njobs <= 0 || W <= 0 || W > 64) return;
+  if (njobs <= 0 || W <= 0) return;
   const int cu = (max_n + 15) / 16, cr = (max_n + 255) / 256;
   hipLaunchKernelGGL(k_dd_inv_super_u, dim3(njobs * cu), dim3(64), 0, st, jobs, s0, W, cu);
   hipLaunchKernelGGL(k_dd_inv_super_r, dim3(njobs * W * cr), dim3(256), 0, st, jobs, s0, W, cr);

@@ -254,11 +254,14 @@ void launch_dd_assemble(hipStream_t st, const RowJob* jobs, const int32_t* row_j
 void launch_dd_inv_panel(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int s0, int sw, int max_n,
                          int32_t* status);
 void launch_dd_inv_unscramble(hipStream_t st, const InvJobDD* jobs, int njobs, int max_n);
-// two-level Gauss-Jordan: T = super-panel columns minus identity (row stride W), R = its pivot rows
+// T = the columns [s0, s0 + W) minus the identity at their pivots (row stride W), R = their pivot rows;
+// jobs that do not update at this level (n <= W, or W = kDDBlock below kDDBlockMin) are skipped
 void launch_dd_inv_super(hipStream_t st, const InvJobDD* jobs, int njobs, int s0, int W, int max_n);
 int dd_inv_nb(int max_n);
-// columns of a super-panel of the double-double Gauss-Jordan (its pivot rows update the rest at once)
-constexpr int kDDSuper = 64;
+// columns of a super-panel and of a block of super-panels of the double-double Gauss-Jordan, and the
+// columns of the T and R workspaces of a matrix of order n
+constexpr int kDDSuper = 64, kDDBlock = 256, kDDBlockMin = 512;
+constexpr int dd_inv_width(int n) { return n > kDDBlockMin ? kDDBlock : kDDSuper; }
 
 // ---- double-double products from int8 residues on the integer matrix cores (ozaki.hip) ----
 // S = 16 (the default) keeps each double-double operand to 2^-112 of its row's (or column's)
@@ -281,7 +284,11 @@ struct OzSplitJob {
   int8_t* out;
   int32_t* ex;
   int32_t tile_off, kper;
+  const int32_t* piv;   // pivot rows of a Gauss-Jordan update, see piv_mode
+  int32_t piv_mode;
 };
+// how a split reads its operand: plain; element (r, k) minus 1 where r = piv[k]; row piv[k] of X for k
+enum { kOzPlain = 0, kOzMinusPivots = 1, kOzPivotRows = 2 };
 constexpr int oz_split_blocks(int Rp, int Kp, int kper) {
   const int chunks = (Kp / 64 + kper - 1) / kper;
   return Rp / 16 * (chunks > 0 ? chunks : 1);

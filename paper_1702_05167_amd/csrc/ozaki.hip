@@ -31,9 +31,9 @@
 // Layout: the residues of one operand are 64 planes of int8 (two per modulus;
 // rows padded to 32, K padded to 64 with zeros), each stored as 1 KB
 // fragments of 16 rows x 64 k in the order in which the matrix cores take an
-// operand, the 64 planes of a fragment (plane h of modulus m: 2 m + h) in a row, the fragments k fastest: what
-// a tile needs for one k step lies in runs of whole fragments, and the split writes 64 KB in a row.
-// Row scales int32 [Rp].
+// operand: per row block of 16, the planes in sixteen slots of four (modulus 2 s and 2 s + 1), per slot
+// the fragments of one k step after the other, four planes each.  A product takes slot after slot,
+// so it reads every row block's data as one stream.  Row scales int32 [Rp].
 #include <hip/hip_runtime.h>
 
 #include "dd.h"
@@ -67,13 +67,33 @@ __device__ __forceinline__ uint32_t res_pack(int a, int b, int c, int d) {
   return __builtin_amdgcn_perm(cd, ab, 0x05040100);
 }
 
+// pointers read from a descriptor are global memory (the compiler would use flat accesses)
+template <class T> using global_ptr = __attribute__((address_space(1))) T*;
+typedef double v2d __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ zdd load_zdd(const zdd* q) {
+  const global_ptr<const v2d> p = (global_ptr<const v2d>)q;
+  const v2d a = p[0], b = p[1];
+  return zdd{dd{a.x, a.y}, dd{b.x, b.y}};
+}
+__device__ __forceinline__ void store_zdd(zdd* q, zdd v) {
+  const global_ptr<v2d> p = (global_ptr<v2d>)q;
+  p[0] = v2d{v.re.hi, v.re.lo};
+  p[1] = v2d{v.im.hi, v.im.lo};
+}
+
 // ---------------------------------------------------------------------------------------------
 // splitting
 
 // element (r, k) of the operand as stored: X[r * ldr + k * ldk]; zero outside R x K
+// (piv_mode: see OzSplitJob)
 __device__ __forceinline__ zdd oz_elem(const OzSplitJob& jb, int r, int k) {
   if (r >= jb.R || k >= jb.K) return zdd_zero();
-  return jb.X[(int64_t)r * jb.ldr + (int64_t)k * jb.ldk];
+  if (jb.piv_mode == kOzPlain) return load_zdd(jb.X + (int64_t)r * jb.ldr + (int64_t)k * jb.ldk);
+  const int p = ((global_ptr<const int32_t>)jb.piv)[k];
+  if (jb.piv_mode == kOzPivotRows) return load_zdd(jb.X + (int64_t)r * jb.ldr + (int64_t)p * jb.ldk);
+  zdd v = load_zdd(jb.X + (int64_t)r * jb.ldr + (int64_t)k * jb.ldk);
+  if (r == p) v.re = dd_add(v.re, dd_from(-1.0));
+  return v;
 }
 
 __device__ __forceinline__ double oz_mag(const zdd& v) {
@@ -160,7 +180,8 @@ __global__ __launch_bounds__(256) void k_oz_split(const OzSplitJob* __restrict__
       cr[u] = oz_chunks(dd{ldexp(nr.hi, sh), ldexp(nr.lo, sh)});
       ci[u] = oz_chunks(dd{ldexp(ni.hi, sh), ldexp(ni.lo, sh)});
     }
-    int8_t* out = jb.out + ((int64_t)rb * kcs + kc) * (kResPlanes * 1024) + 256 * w + 16 * ri + 4 * g;
+    int8_t* out = jb.out + (int64_t)rb * kcs * (kResPlanes * 1024) + kc * 4096 + 256 * w + 16 * ri + 4 * g;
+    const int slot = kcs * 4096;
 #pragma unroll
     for (int q = 0; q < kResMods / 4; ++q)
 #pragma unroll
@@ -178,7 +199,7 @@ __global__ __launch_bounds__(256) void k_oz_split(const OzSplitJob* __restrict__
         for (int j = 0; j < 4; ++j) {
           const int m = 4 * q + j, p = kResModuli[m];
           const float inv = 1.0f / (float)p;
-          *reinterpret_cast<uint32_t*>(out + (2 * m + pl) * 1024) =
+          *reinterpret_cast<uint32_t*>(out + (m >> 1) * slot + (2 * (m & 1) + pl) * 1024) =
               res_pack(res_byte(s[0][j], p, inv), res_byte(s[1][j], p, inv), res_byte(s[2][j], p, inv),
                        res_byte(s[3][j], p, inv));
         }
@@ -202,19 +223,6 @@ __device__ __forceinline__ const int8_t* uniform(const int8_t* p) {   // a wave-
   const uint64_t v = (uint64_t)p;
   return (const int8_t*)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
                          (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
-}
-// pointers read from a descriptor are global memory (the compiler would use flat accesses)
-template <class T> using global_ptr = __attribute__((address_space(1))) T*;
-typedef double v2d __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ zdd load_zdd(const zdd* q) {
-  const global_ptr<const v2d> p = (global_ptr<const v2d>)q;
-  const v2d a = p[0], b = p[1];
-  return zdd{dd{a.x, a.y}, dd{b.x, b.y}};
-}
-__device__ __forceinline__ void store_zdd(zdd* q, zdd v) {
-  const global_ptr<v2d> p = (global_ptr<v2d>)q;
-  p[0] = v2d{v.re.hi, v.re.lo};
-  p[1] = v2d{v.im.hi, v.im.lo};
 }
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
@@ -282,7 +290,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   // wave w stages plane w of the slot's four: four row blocks of A (the last one again past the end of
   // an operand that is not a multiple of 64) and two of B
-  const uint32_t frag = kResPlanes * 1024, row = kcs * frag;
+  const uint32_t row = kcs * (kResPlanes * 1024);   // bytes of a row block
   const int8_t* const baseA = uniform(pr.A8 + (int64_t)(m0 / 16) * row + w * 1024);
   const int8_t* const baseB = uniform(pr.B8 + (int64_t)(n0 / 16) * row + w * 1024);
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(lds)) + w * 6144;
@@ -291,11 +299,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int f = 0; f < 4; ++f) off[f] = min(f, pr.Mp / 16 - m0 / 16 - 1) * row + 16 * lane;
   // loads of the next step; past the last one, the last again (its buffer is not read any more)
   uint32_t pos = 0, to = 0;             // of the loads within the row blocks, and in LDS
-  const uint32_t last = row - frag + 15 * 4096;
   auto advance = [&]() {
     to = to == (kRing - 1) * kStage ? 0 : to + kStage;
-    const uint32_t next = pos + frag;
-    pos = __builtin_amdgcn_readfirstlane(pos == last ? last : next >= row ? next - row + 4096 : next);
+    pos = __builtin_amdgcn_readfirstlane(min(pos + 4096, row - 4096));
   };
 
   uint32_t rre[4][4][4], rim[4][4][4];   // residues: [block of 16 x 16][register][word of four slots]

@@ -327,10 +327,10 @@ struct Builder {
       for (int e = 0; e < B; ++e) {
         CS& s = cs[(size_t)i * B + e];
         if (ddf) {
-          const size_t nbd = dd_inv_nb((int)n);
+          const size_t w = dd_inv_width((int)n);
           s.Fd = wsa((n + f) * (n + f) * 32);
-          s.Td = wsa(n * std::max<size_t>(nbd, kDDSuper) * 32);
-          s.Rd = wsa(std::max<size_t>(nbd, kDDSuper) * n * 32);
+          s.Td = wsa(n * w * 32);
+          s.Rd = wsa(w * n * 32);
         } else {
           s.F = wsa((n + f) * (n + f) * 16);
           s.T = wsa(n * 4 * nb * 16);   // panel T (n x nb) and super-panel U (n x 4 nb)
@@ -621,6 +621,8 @@ struct Builder {
   struct GPD {
     const zdd *A, *B, *C; zdd* D; double2* D64; int M, N, K, lda, ldb, ldc, ldd, ldd64;
     size_t sa = 0;   // workspace offset of op(A)'s kept slices (0: split into the step's scratch)
+    // Gauss-Jordan update (matrix cores): A minus the identity at the rows piv[k], B's row k is piv[k]
+    const int32_t* piv = nullptr;
   };
   std::vector<size_t> oz_kept;   // kept slice buffers already split by an earlier step
   // Double-double block products: with `oz`, every problem whose depth K lies in
@@ -667,7 +669,9 @@ struct Builder {
       // slices of one operand: in the step's scratch (offsets rebased later, `kept` false) or in a
       // workspace buffer kept for later products (absolute addresses, split by the first step using it)
       std::vector<char> kept_job;   // per split job: writes a kept buffer
-      auto operand = [&](const zdd* X, int64_t ldr, int64_t ldk, int R, int K, size_t keep) {
+      auto operand = [&](const zdd* X, int64_t ldr, int64_t ldk, int R, int K, size_t keep, const int32_t* piv,
+                         int piv_mode) {
+        // (a pivoted operand is no other product's plain one: its step has Gauss-Jordan updates only)
         const auto key = std::make_tuple((const void*)X, ldr, ldk, R, K);
         auto it = seen.find(key);
         if (it != seen.end()) return it->second;
@@ -685,6 +689,7 @@ struct Builder {
         }
         OzSplitJob j{};
         j.X = X; j.ldr = ldr; j.ldk = ldk; j.R = R; j.K = K; j.Rp = Rp; j.Kp = Kp;
+        j.piv = piv; j.piv_mode = piv ? piv_mode : kOzPlain;
         j.out = reinterpret_cast<int8_t*>(off);
         j.ex = reinterpret_cast<int32_t*>(off + (size_t)kOzPlanes * Rp * Kp);
         kept_job.push_back(keep ? 1 : 0);
@@ -699,8 +704,10 @@ struct Builder {
         if (g.M <= 0 || g.N <= 0) continue;
         const size_t need = (g.sa ? 0 : oz_bytes(g.M, g.K)) + oz_bytes(g.N, g.K);
         if (i > i0 && cur + need > kOzStepCap) break;
-        const auto a = opA == 0 ? operand(g.A, g.lda, 1, g.M, g.K, g.sa) : operand(g.A, 1, g.lda, g.M, g.K, g.sa);
-        const auto b = opB == 0 ? operand(g.B, 1, g.ldb, g.N, g.K, 0) : operand(g.B, g.ldb, 1, g.N, g.K, 0);
+        const auto a = opA == 0 ? operand(g.A, g.lda, 1, g.M, g.K, g.sa, g.piv, kOzMinusPivots)
+                                : operand(g.A, 1, g.lda, g.M, g.K, g.sa, nullptr, kOzPlain);
+        const auto b = opB == 0 ? operand(g.B, 1, g.ldb, g.N, g.K, 0, g.piv, kOzPivotRows)
+                                : operand(g.B, g.ldb, 1, g.N, g.K, 0, nullptr, kOzPlain);
         kept_a.push_back(g.sa ? 1 : 0);
         GemmProbOZ p{};
         p.A8 = reinterpret_cast<const int8_t*>(a.first);
@@ -805,41 +812,61 @@ struct Builder {
     push(s);
   }
 
-  // Batched Gauss-Jordan inverses in double-double (the pivot blocks A_ii^-1 of Algorithm 1), two
-  // levels: panels of nb columns inside super-panels of kDDSuper columns; a panel's rank-nb update
-  // touches only its super-panel's columns (vector units), and each super-panel then updates every
-  // other column at once with its pivot rows (a rank-kDDSuper product, on the integer matrix cores
-  // with `oz`).  Jobs need T (n x kDDSuper) and R (kDDSuper x n) workspaces.
+  // Batched Gauss-Jordan inverses in double-double (the pivot blocks A_ii^-1 of Algorithm 1): panels of
+  // nb columns inside super-panels of kDDSuper; a panel's rank-nb update touches only its super-panel's
+  // columns (vector units), a super-panel's rank-kDDSuper update every other column (integer matrix
+  // cores with `oz`).  Blocks beyond kDDBlockMin take a third level: a super-panel updates only its
+  // block of kDDBlock columns and each block the rest, since a product of depth 256 runs at twice the
+  // rate of one of depth 64 (below that the narrow remainders and the second split cost as much as it saves).
+  // Products on the matrix cores split their operands straight from X; those on the vector units need
+  // the T (n x dd_inv_width(n)) and R (its transpose's shape) workspaces.
   void dd_inverse(const std::vector<InvJobDD>& ij, int maxn) {
     const int nb = dd_inv_nb(maxn);
     const size_t ijo = blob.push(ij);
-    const int SW = kDDSuper;
-    for (int s0 = 0; s0 < maxn; s0 += SW) {
-      for (int k0 = s0; k0 < std::min(s0 + SW, maxn); k0 += nb) {
-        Step p; p.kind = S_DD_INV_PANEL; p.jobs = ijo; p.njobs = (int)ij.size(); p.i0 = k0; p.i1 = s0; p.i2 = maxn;
-        push(p);
-        if (maxn <= nb) continue;   // no other columns
-        std::vector<GPD> ps;
-        for (const InvJobDD& j : ij) {
-          if (k0 >= j.n) continue;
-          const int kb = std::min(nb, j.n - k0);
-          const int ns = std::min(s0 + SW, j.n) - s0;
-          ps.push_back({j.T, j.R + s0, j.X + s0, j.X + s0, nullptr, j.n, ns, kb, kb, j.n, j.ld, j.ld, 0});
-        }
-        dd_gemm_valu(0, 0, ps, 0, 1);
-      }
-      Step sp; sp.kind = S_DD_INV_SUPER; sp.jobs = ijo; sp.njobs = (int)ij.size(); sp.i0 = s0; sp.i1 = SW; sp.i2 = maxn;
-      push(sp);
-      std::vector<GPD> pt;
+    // the columns [s0, s0 + w) applied to the other columns of the super-panel's block (w = kDDSuper) or of
+    // the matrix (w = kDDBlock, blocked matrices only)
+    auto update = [&](int s0, int w) {
+      std::vector<GPD> on, off;
       for (const InvJobDD& j : ij) {
-        if (s0 >= j.n) continue;
-        const int ws = std::min(SW, j.n - s0);
-        if (s0 > 0) pt.push_back({j.T, j.R, j.X, j.X, nullptr, j.n, s0, ws, SW, j.n, j.ld, j.ld, 0});
-        if (s0 + ws < j.n)
-          pt.push_back({j.T, j.R + s0 + ws, j.X + s0 + ws, j.X + s0 + ws, nullptr, j.n, j.n - s0 - ws, ws, SW, j.n,
-                        j.ld, j.ld, 0});
+        const bool blocked = dd_inv_width(j.n) == kDDBlock;
+        if (s0 >= j.n || (w == kDDBlock && !blocked)) continue;
+        const bool inner = w == kDDSuper && blocked;
+        const int lo = inner ? s0 / kDDBlock * kDDBlock : 0, hi = inner ? std::min(lo + kDDBlock, j.n) : j.n;
+        const int ws = std::min(w, j.n - s0);
+        for (int side = 0; side < 2; ++side) {
+          const int c0 = side == 0 ? lo : s0 + ws, c1 = side == 0 ? s0 : hi;
+          if (c0 >= c1) continue;
+          GPD g{j.X + s0, j.X + c0, j.X + c0, j.X + c0, nullptr, j.n, c1 - c0, ws, j.ld, j.ld, j.ld, j.ld, 0};
+          g.piv = j.piv + s0;
+          if (oz && oz_pays(g)) { on.push_back(g); continue; }
+          off.push_back({j.T, j.R + c0, j.X + c0, j.X + c0, nullptr, j.n, c1 - c0, ws, w, j.n, j.ld, j.ld, 0});
+        }
       }
-      dd_gemm(0, 0, pt, 0, 1);
+      // the copies first: the products on the matrix cores change X
+      if (!off.empty()) {
+        Step sp; sp.kind = S_DD_INV_SUPER; sp.jobs = ijo; sp.njobs = (int)ij.size(); sp.i0 = s0; sp.i1 = w; sp.i2 = maxn;
+        push(sp);
+      }
+      if (!on.empty()) oz_gemm(0, 0, on, 0, 1);
+      if (!off.empty()) dd_gemm_valu(0, 0, off, 0, 1);
+    };
+    for (int b0 = 0; b0 < maxn; b0 += kDDBlock) {
+      for (int s0 = b0; s0 < std::min(b0 + kDDBlock, maxn); s0 += kDDSuper) {
+        for (int k0 = s0; k0 < std::min(s0 + kDDSuper, maxn); k0 += nb) {
+          Step p; p.kind = S_DD_INV_PANEL; p.jobs = ijo; p.njobs = (int)ij.size(); p.i0 = k0; p.i1 = s0; p.i2 = maxn;
+          push(p);
+          std::vector<GPD> ps;
+          for (const InvJobDD& j : ij) {
+            if (k0 >= j.n) continue;
+            const int kb = std::min(nb, j.n - k0);
+            const int ns = std::min(s0 + kDDSuper, j.n) - s0;
+            if (ns > kb) ps.push_back({j.T, j.R + s0, j.X + s0, j.X + s0, nullptr, j.n, ns, kb, kb, j.n, j.ld, j.ld, 0});
+          }
+          dd_gemm_valu(0, 0, ps, 0, 1);
+        }
+        update(s0, kDDSuper);
+      }
+      update(b0, kDDBlock);
     }
     Step u; u.kind = S_DD_INV_UNSCR; u.jobs = ijo; u.njobs = (int)ij.size(); u.i2 = maxn;
     push(u);
@@ -2858,7 +2885,7 @@ hsc_status hsc_kern_zinv_dd(hsc_ctx* ctx, int32_t n, void* X, int32_t ld, void* 
   }
   HIPCHK(hipSetDevice(ctx->device));
   // the solver's own inverse steps (Builder::dd_inverse) for one block
-  const size_t W = std::max<size_t>(dd_inv_nb(n), kDDSuper);
+  const size_t W = dd_inv_width(n);
   size_t ws = 0;
   auto wa = [&](size_t b) { size_t o = (ws + 255) / 256 * 256; ws = o + b; return o; };
   const size_t o_piv = wa(2 * sizeof(int32_t) * n), o_t = wa(32 * W * n), o_r = wa(32 * W * n);
