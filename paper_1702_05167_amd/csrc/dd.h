@@ -101,6 +101,29 @@ __device__ __forceinline__ zdd zdd_rcp(zdd a) {
   return zdd{dd{ldexp(re.hi, e), ldexp(re.lo, e)}, dd{ldexp(im.hi, e), ldexp(im.lo, e)}};
 }
 
+// Pointers loaded from a descriptor are generic to the compiler; as global ones they give global loads and
+// stores instead of flat ones (which also wait for LDS).
+typedef double v2d __attribute__((ext_vector_type(2)));
+template <class T> using global_ptr = __attribute__((address_space(1))) T*;
+// memory that nothing writes while the kernel runs: loads at wave-uniform addresses are scalar
+template <class T> using const_ptr = const __attribute__((address_space(4))) T*;
+
+__device__ __forceinline__ zdd load_zdd(const zdd* q) {
+  const global_ptr<const v2d> p = (global_ptr<const v2d>)q;
+  const v2d re = p[0], im = p[1];
+  return zdd{dd{re.x, re.y}, dd{im.x, im.y}};
+}
+__device__ __forceinline__ zdd load_zdd(const_ptr<zdd> q) {
+  const const_ptr<v2d> p = (const_ptr<v2d>)q;
+  const v2d re = p[0], im = p[1];
+  return zdd{dd{re.x, re.y}, dd{im.x, im.y}};
+}
+__device__ __forceinline__ void store_zdd(zdd* q, zdd v) {
+  const global_ptr<v2d> p = (global_ptr<v2d>)q;
+  p[0] = v2d{v.re.hi, v.re.lo};
+  p[1] = v2d{v.im.hi, v.im.lo};
+}
+
 // Lazy accumulation of a sum of double-double products (the GEMM inner loop): hi
 // holds the running FP64 sum, lo collects the exact rounding errors of the hi
 // additions (two_sum) and the products' low parts in plain FP64.  renorm() folds
@@ -146,6 +169,7 @@ __device__ __forceinline__ void zddacc_renorm(zddacc& c) {
   ddacc_renorm(c.im);
 }
 
+__device__ __forceinline__ zddacc zddacc_from(zdd v) { return zddacc{{v.re.hi, v.re.lo}, {v.im.hi, v.im.lo}}; }
 __device__ __forceinline__ zdd zddacc_value(zddacc c) { return zdd{two_sum(c.re.hi, c.re.lo), two_sum(c.im.hi, c.im.lo)}; }
 
 __device__ __forceinline__ double zdd_cabs1(zdd a) { return fabs(a.re.hi) + fabs(a.im.hi); }

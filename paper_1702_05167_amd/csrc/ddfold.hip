@@ -98,8 +98,9 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 // leading 8 mantissa bits (and exponent) of |Re| + |Im|, the first of equals: one 32-bit key per row, one
 // maximum.  Every thread forms the reciprocal itself (no round trip through LDS), and the columns
 // rotate through the registers so that the step's code is a loop body (the current column is P[.][0]).
-// Also written: T = the panel's columns minus the identity at the pivots, R = the pivot rows' old values in
-// the other columns of the super-panel [s0, s1) (zero in the panel's own), the factors of its update.
+// Also written: T (NB x n) = the panel's columns minus the identity at the pivots, as rows, and R (NB x n) =
+// the pivot rows' old values in the other columns of the super-panel (zero in the panel's own and, in both,
+// beyond its nb columns), the factors of its update.
 template <int TH, int RPT, int NB>
 __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_dd_inv_panel(
     const InvJobDD* __restrict__ jobs, int k0, int s0, int sw, int32_t* __restrict__ status) {
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void
       const zdd b = rowp[par][jj];
 #pragma unroll
       for (int q = 0; q < RPT; ++q) {
-        zddacc a{{P[q][jj].re.hi, P[q][jj].re.lo}, {P[q][jj].im.hi, P[q][jj].im.lo}};
+        zddacc a = zddacc_from(P[q][jj]);
         zddacc_fma(a, g[q], b);
         P[q][jj - 1] = zddacc_value(a);
       }
@@ -186,22 +187,89 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         const int j = i + nb < NB ? i + nb : i + nb - NB;
+        zdd v = zdd_zero();
         if (j < nb) {
-          zdd v = P[q][i];
+          v = P[q][i];
           jb.X[(int64_t)r * jb.ld + k0 + j] = v;
           if (r == prows[j]) v.re = dd_add(v.re, dd_from(-1.0));
-          jb.T[(int64_t)r * nb + j] = v;
         }
+        jb.T[(int64_t)j * n + r] = v;
       }
     }
   }
   if (t < nb) jb.piv[k0 + t] = prows[t];
   const int ws = min(s0 + sw, n) - s0;
-  for (int i = t; i < nb * ws; i += TH) {
+  for (int i = t; i < NB * ws; i += TH) {
     const int j = i / ws, c = s0 + i % ws;
-    jb.R[(int64_t)j * n + c] = (c >= k0 && c < k0 + nb) ? zdd_zero() : jb.X[(int64_t)prows[j] * jb.ld + c];
+    jb.R[(int64_t)j * n + c] =
+        (j >= nb || (c >= k0 && c < k0 + nb)) ? zdd_zero() : jb.X[(int64_t)prows[j] * jb.ld + c];
   }
   if (t == 0 && bad && status) atomicMin(&status[jb.e], (int32_t)HSC_E_SINGULAR);
+}
+
+// X[r][c] += sum_k T[k][r] R[k][c] over the super-panel's columns [s0, s0 + ns): a lane holds one column
+// and its NB values of R, a wave walks rows, whose T values wait in LDS.  Super-panels of at most 32 or 16
+// columns (the last of a matrix) put 2 or 4 rows side by side in a wave.  Bound by the vector units: 50 FP64
+// instructions per complex multiply-add, 1.74 ps at their measured 2.3 ns a wave; 512 matrices of order 216
+// take 122 us (2.15 ps, 3.7 TB/s of X), 1024 of order 64 62 us (1.86 ps).  The grouped product that this
+// replaces took 158 us, and 13 us against 7 us for one small matrix.
+constexpr int kRankRows = 32;   // rows of a workgroup at most
+
+template <int NB, int CW>
+__device__ __forceinline__ void inv_rank_rows(const InvJobDD& jb, const zdd* T, int s0, int ns, int r0, int rows,
+                                              int lane) {
+  constexpr int RS = 64 / CW;   // rows side by side
+  const int n = jb.n, c = lane % CW, q = lane / CW;
+  if (c >= ns) return;
+  const int64_t ld = jb.ld;
+  const zdd* R = jb.R + s0 + c;
+  zdd* X = jb.X + r0 * ld + s0 + c;
+  const int last = rows - 1;
+  int i = q;
+  // (rows beyond the end are read at the last one and not written)
+  zdd x0 = load_zdd(X + min(i, last) * ld), x1 = load_zdd(X + min(i + RS, last) * ld);
+  zdd b[NB];
+#pragma unroll
+  for (int k = 0; k < NB; ++k) b[k] = load_zdd(R + (int64_t)k * n);
+#pragma unroll 1
+  for (;;) {
+    const zdd y0 = load_zdd(X + min(i + 2 * RS, last) * ld), y1 = load_zdd(X + min(i + 3 * RS, last) * ld);
+    zddacc a0 = zddacc_from(x0), a1 = zddacc_from(x1);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      zddacc_fma(a0, T[min(i, last) * NB + k], b[k]);
+      zddacc_fma(a1, T[min(i + RS, last) * NB + k], b[k]);
+    }
+    if (i < rows) store_zdd(X + i * ld, zddacc_value(a0));
+    if (i + RS < rows) store_zdd(X + (i + RS) * ld, zddacc_value(a1));
+    i += 2 * RS;
+    if (i >= rows) return;
+    x0 = y0;
+    x1 = y1;
+  }
+}
+
+template <int NB>
+__global__ __launch_bounds__(256) void k_dd_inv_rank(const InvJobDD* __restrict__ jobs, int k0, int s0, int sw,
+                                                     int rows_w, int chunks) {
+  __shared__ zdd T[kRankRows * NB];
+  const InvJobDD jb = jobs[blockIdx.x / chunks];
+  const int n = jb.n, ns = min(s0 + sw, n) - s0;
+  const int b0 = (int)(blockIdx.x % chunks) * 4 * rows_w;
+  if (k0 >= n || ns <= NB || b0 >= n) return;   // (at most NB columns: no others)
+  const int rows_b = min(4 * rows_w, n - b0);
+  for (int i = threadIdx.x; i < 4 * rows_w * NB; i += 256) {
+    const int k = i / (4 * rows_w), r = i % (4 * rows_w);
+    if (r < rows_b) T[r * NB + k] = load_zdd(jb.T + (int64_t)k * n + b0 + r);
+  }
+  __syncthreads();
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int rows = min(rows_w, rows_b - w * rows_w);
+  if (rows <= 0) return;
+  const zdd* Tw = T + w * rows_w * NB;
+  if (ns > 32) inv_rank_rows<NB, 64>(jb, Tw, s0, ns, b0 + w * rows_w, rows, lane);
+  else if (ns > 16) inv_rank_rows<NB, 32>(jb, Tw, s0, ns, b0 + w * rows_w, rows, lane);
+  else inv_rank_rows<NB, 16>(jb, Tw, s0, ns, b0 + w * rows_w, rows, lane);
 }
 
 // After the panels of the columns [s0, s0 + ws), ws <= W, of a matrix with other columns to update:
@@ -544,6 +612,20 @@ void launch_dd_inv_panel(hipStream_t st, const InvJobDD* jobs, int njobs, int k0
   else if (max_n <= 1024) hipLaunchKernelGGL((k_dd_inv_panel<512, 2, 8>), g, dim3(512), 0, st, jobs, k0, s0, sw, status);
   else if (max_n <= 2048) hipLaunchKernelGGL((k_dd_inv_panel<512, 4, 4>), g, dim3(512), 0, st, jobs, k0, s0, sw, status);
   else hipLaunchKernelGGL((k_dd_inv_panel<512, 8, 2>), g, dim3(512), 0, st, jobs, k0, s0, sw, status);
+}
+
+void launch_dd_inv_rank(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int s0, int sw, int max_n) {
+  if (njobs <= 0 || k0 >= max_n) return;
+  // 8 rows of a wave share its R values (122 us for 512 matrices of order 216, 133 us with 4 and 158 us with
+  // 2); fewer where that leaves under 3 waves per SIMD (18 of order 960: 26 us with 8, 23 us with 4)
+  int rows_w = kRankRows / 4;
+  while (rows_w > 2 && (int64_t)njobs * ((max_n + rows_w - 1) / rows_w) < 3072) rows_w /= 2;
+  const int chunks = (max_n + 4 * rows_w - 1) / (4 * rows_w);
+  const dim3 g((unsigned)(njobs * chunks)), b(256);
+  const int nb = dd_inv_nb(max_n);
+  if (nb == 8) hipLaunchKernelGGL((k_dd_inv_rank<8>), g, b, 0, st, jobs, k0, s0, sw, rows_w, chunks);
+  else if (nb == 4) hipLaunchKernelGGL((k_dd_inv_rank<4>), g, b, 0, st, jobs, k0, s0, sw, rows_w, chunks);
+  else hipLaunchKernelGGL((k_dd_inv_rank<2>), g, b, 0, st, jobs, k0, s0, sw, rows_w, chunks);
 }
 
 void launch_dd_inv_super(hipStream_t st, const InvJobDD* jobs, int njobs, int s0, int W, int max_n) {

@@ -253,6 +253,8 @@ void launch_dd_assemble(hipStream_t st, const RowJob* jobs, const int32_t* row_j
 // with T and R the factors of the update of the super-panel's other columns
 void launch_dd_inv_panel(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int s0, int sw, int max_n,
                          int32_t* status);
+// its update of the super-panel's other columns
+void launch_dd_inv_rank(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int s0, int sw, int max_n);
 void launch_dd_inv_unscramble(hipStream_t st, const InvJobDD* jobs, int njobs, int max_n);
 // T = the columns [s0, s0 + W) minus the identity at their pivots (row stride W), R = their pivot rows;
 // jobs that do not update at this level (n <= W, or W = kDDBlock below kDDBlockMin) are skipped

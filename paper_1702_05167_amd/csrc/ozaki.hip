@@ -67,20 +67,6 @@ __device__ __forceinline__ uint32_t res_pack(int a, int b, int c, int d) {
   return __builtin_amdgcn_perm(cd, ab, 0x05040100);
 }
 
-// pointers read from a descriptor are global memory (the compiler would use flat accesses)
-template <class T> using global_ptr = __attribute__((address_space(1))) T*;
-typedef double v2d __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ zdd load_zdd(const zdd* q) {
-  const global_ptr<const v2d> p = (global_ptr<const v2d>)q;
-  const v2d a = p[0], b = p[1];
-  return zdd{dd{a.x, a.y}, dd{b.x, b.y}};
-}
-__device__ __forceinline__ void store_zdd(zdd* q, zdd v) {
-  const global_ptr<v2d> p = (global_ptr<v2d>)q;
-  p[0] = v2d{v.re.hi, v.re.lo};
-  p[1] = v2d{v.im.hi, v.im.lo};
-}
-
 // ---------------------------------------------------------------------------------------------
 // splitting
 

@@ -65,8 +65,8 @@ struct Blob {
 
 enum StepKind { S_ASSEMBLE, S_INV_PANEL, S_INV_SWAP, S_INV_UNSCR, S_GEMM, S_GATHER, S_ASSEMBLE_N, S_DIAG, S_GUARD,
                 S_DD_ASSEMBLE, S_DD_INV_PANEL, S_DD_INV_SWAP, S_DD_INV_UNSCR, S_DD_GEMM, S_INV_SUPER,
-                S_OZ_SPLIT, S_OZ_GEMM, S_DD_INV_SUPER, S_FACE_HALF, S_FACE_SIGMA, S_BONDS};
-constexpr int kStepKinds = 21;
+                S_OZ_SPLIT, S_OZ_GEMM, S_DD_INV_SUPER, S_FACE_HALF, S_FACE_SIGMA, S_BONDS, S_DD_INV_RANK};
+constexpr int kStepKinds = 22;
 
 // Tile sizes a plan keeps GEMM problem lists and tile maps for: 64x64, 128x64, 64x128, 32x32,
 // 128x128.  Every launch kind of launch_gemm uses one of them (tile_dims_of).
@@ -855,14 +855,15 @@ struct Builder {
         for (int k0 = s0; k0 < std::min(s0 + kDDSuper, maxn); k0 += nb) {
           Step p; p.kind = S_DD_INV_PANEL; p.jobs = ijo; p.njobs = (int)ij.size(); p.i0 = k0; p.i1 = s0; p.i2 = maxn;
           push(p);
-          std::vector<GPD> ps;
+          Step r = p; r.kind = S_DD_INV_RANK;
+          bool others = false;
           for (const InvJobDD& j : ij) {
-            if (k0 >= j.n) continue;
-            const int kb = std::min(nb, j.n - k0);
-            const int ns = std::min(s0 + kDDSuper, j.n) - s0;
-            if (ns > kb) ps.push_back({j.T, j.R + s0, j.X + s0, j.X + s0, nullptr, j.n, ns, kb, kb, j.n, j.ld, j.ld, 0});
+            const int kb = std::min(nb, j.n - k0), ns = std::min(s0 + kDDSuper, j.n) - s0;
+            if (kb <= 0 || ns <= nb) continue;
+            others = true;
+            r.flops += 8.0 * j.n * ns * kb;
           }
-          dd_gemm_valu(0, 0, ps, 0, 1);
+          if (others) push(r);
         }
         update(s0, kDDSuper);
       }
@@ -1550,7 +1551,7 @@ const int kKinds3[] = {4, 5, 7, 8};
 bool step_empty(const Step& s) {
   switch (s.kind) {
     case S_INV_PANEL: case S_INV_SWAP: case S_INV_UNSCR: case S_INV_SUPER: case S_GUARD:
-    case S_DD_INV_PANEL: case S_DD_INV_UNSCR: case S_DD_INV_SUPER:
+    case S_DD_INV_PANEL: case S_DD_INV_UNSCR: case S_DD_INV_SUPER: case S_DD_INV_RANK:
     case S_FACE_HALF: case S_FACE_SIGMA:
       return s.njobs <= 0;
     case S_BONDS:
@@ -1624,6 +1625,9 @@ int run_steps(hsc_ctx* ctx, hipStream_t st, Plan* pl, int e_base, int nvalid, vo
         break;
       case S_DD_INV_PANEL:
         launch_dd_inv_panel(st, (const InvJobDD*)jobs, s.njobs, s.i0, s.i1, kDDSuper, s.i2, pl->status);
+        break;
+      case S_DD_INV_RANK:
+        launch_dd_inv_rank(st, (const InvJobDD*)jobs, s.njobs, s.i0, s.i1, kDDSuper, s.i2);
         break;
       case S_DD_INV_UNSCR:
         launch_dd_inv_unscramble(st, (const InvJobDD*)jobs, s.njobs, s.i2);

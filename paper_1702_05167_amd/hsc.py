@@ -173,7 +173,7 @@ class Context:
     PROFILE_KINDS = ("assemble", "inv_panel", "inv_swap", "inv_unscramble", "gemm", "gather",
                      "assemble_n", "diag", "guard", "dd_assemble", "dd_inv_panel", "dd_inv_swap",
                      "dd_inv_unscramble", "dd_gemm", "inv_super", "oz_split", "oz_gemm", "dd_inv_super",
-                     "face_half", "face_sigma", "bonds")
+                     "face_half", "face_sigma", "bonds", "dd_inv_rank")
 
     def profile_bytes(self) -> dict:
         """Algorithmic bytes per launch kind since profiling was enabled (slice products only)."""
