@@ -633,8 +633,11 @@ struct Builder {
   static constexpr size_t kOzStepCap = size_t(4) << 30;   // slice scratch of one product step
   // Measured costs on the target (seconds): splitting one complex double-double element into
   // residues, one padded multiply-add and one output of the residue product, one multiply-add on the
-  // vector units.
-  static constexpr double kOzSplitCost = 25e-12, kOzMacCost = 0.1e-12, kOzOutCost = 12e-12, kValuMacCost = 1.5e-12;
+  // vector units (1.5 ps in full tiles, 2.2-3.6 ps in the products of small trees).  A forest of 8 devices
+  // of sides 8 to 16 at 16 energies with the last at 1.5, 1.8, 2.4 and 3.5 ps: 45.4, 45.0, 44.2 and 43.7 ms;
+  // one 8^3 device at one energy 1.49, 1.50, 1.49 and 1.68 ms, its few tiles leave the chip idle in the
+  // split's extra launch.
+  static constexpr double kOzSplitCost = 24e-12, kOzMacCost = 0.17e-12, kOzOutCost = 18e-12, kValuMacCost = 2.4e-12;
   bool oz_pays(const GPD& g) const {
     if (g.K < kOzMinK || g.K > oz_max_depth(slices)) return false;
     const double Mp = oz_rows(g.M), Np = oz_rows(g.N), Kp = oz_round(g.K, 64);
