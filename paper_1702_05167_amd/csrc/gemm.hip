@@ -23,6 +23,8 @@
 // MFMA-only stream), at the price of four times the A operand reads.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "kern.h"
 
 namespace hsc {
@@ -99,6 +101,11 @@ struct TileLoader {
   }
 };
 
+// Bound by the matrix cores for deep products (the default 64x64 tile), by C and D for shallow ones.  Edge tiles
+// leave out the 16 x 16 blocks without outputs, and C is on its way while the product is formed (two
+// workgroups per CU, LDS sets that: the registers are there).  Grouped products of a 24^3 transverse tree,
+// before and after, M x N x K: 144 x 1248 x 408 42 -> 48 TFLOP/s, 72 x 1368 x 264 31 -> 38, 12 x 1440 x 192
+// 11 -> 18; with C added 264 x 1368 x 72 30 -> 38, 192 x 192 x 144 44 -> 48, 192 x 1440 x 12 10 -> 15 (4.9 TB/s).
 template <int BM, int BN, int BK, int OPA, int OPB, bool M3, bool MF4 = false, int WGM = 2, int WGN = 2>
 __global__ __launch_bounds__(64 * WGM * WGN) void k_zgemm(const GemmProb* __restrict__ probs,
                                                          const int32_t* __restrict__ tile_prob, int total_tiles,
@@ -121,8 +128,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_zgemm(const GemmProb* __rest
   const int m0 = (local / pr.tiles_n) * BM, n0 = (local % pr.tiles_n) * BN;
   const int M = pr.M, N = pr.N, K = pr.K;
 
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  // every other edge tile hands its blocks to the waves the other way round: the waves that get few of them
+  // do not always sit on the same SIMDs
+  const bool edge = MB * NB > 1 && (M - m0 < BM || N - n0 < BN);
+  const int t = threadIdx.x, lane = t & 63, w0 = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int w = edge && (tile & 1) ? WGM * WGN - 1 - w0 : w0;
   const int wm = w / WGN, wn = w % WGN;
+  // 16 x 16 blocks of this wave with outputs (a single one is formed in any case)
+  const int mb = min(MB, max(0, (M - m0 - wm * WTM + 15) / 16)), nb = min(NB, max(0, (N - n0 - wn * WTN + 15) / 16));
 
   // 16x16x4 form: v4d accumulators; 4x4x4 form: the same registers as four doubles (one per I)
   v4d cr[MB][NB], ci[MB][NB], cs[M3 ? MB : 1][M3 ? NB : 1];   // cs: T3 of the 3-product form
@@ -144,88 +157,115 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_zgemm(const GemmProb* __rest
     la.template store<AS>(As[0], t);
     lb.template store<BS>(Bs[0], t);
   }
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) {
-      la.load(pr.A, pr.lda, m0, (kt + 1) * BK, M, K, OPA == OP_C, t);
-      lb.load(pr.B, pr.ldb, n0, (kt + 1) * BK, N, K, OPB == OP_C, t);
-    }
-    const double2* __restrict__ as = As[cur];
-    const double2* __restrict__ bs = Bs[cur];
+  // C of the small tiles comes with the first operands
+  constexpr bool kEarlyC = MB * NB <= 4;
+  double2 old[kEarlyC ? MB : 1][kEarlyC ? NB : 1][4];
+  if (kEarlyC && beta) {
 #pragma unroll
-    for (int kk = 0; kk < BK / 4; ++kk) {
-      const int k = kk * 4 + (lane >> 4);
-      if (MF4) {
-        double2 b[NB], a4[MB][4];
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j) b[j] = bs[k * BS + wn * WTN + j * 16 + (lane & 15)];
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int I = 0; I < 4; ++I) a4[i][I] = as[k * AS + wm * WTM + i * 16 + 4 * I + (lane & 3)];
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int I = 0; I < 4; ++I) {
-              const double2 x = a4[i][I], y = b[j];
-              if (M3) {
-                cr[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.x, y.x, cr[i][j][I], 0, 0, 0);
-                ci[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.y, y.y, ci[i][j][I], 0, 0, 0);
-                cs[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.x + x.y, y.x + y.y, cs[i][j][I], 0, 0, 0);
-              } else {
-                cr[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.x, y.x, cr[i][j][I], 0, 0, 0);
-                ci[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.x, y.y, ci[i][j][I], 0, 0, 0);
-                cr[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.y, -y.y, cr[i][j][I], 0, 0, 0);
-                ci[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.y, y.x, ci[i][j][I], 0, 0, 0);
-              }
-            }
-        continue;
-      }
-      double2 a[MB], b[NB];
-      double nbi[NB];
-#pragma unroll
-      for (int i = 0; i < MB; ++i) a[i] = as[k * AS + wm * WTM + i * 16 + (lane & 15)];
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        b[j] = bs[k * BS + wn * WTN + j * 16 + (lane & 15)];
-        nbi[j] = -b[j].y;
-      }
-      if (M3) {
-        // cr = T1 (Ar Br), ci = T2 (Ai Bi), cs = T3 ((Ar + Ai)(Br + Bi))
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int j = 0; j < NB; ++j) {
-            cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, cr[i][j], 0, 0, 0);
-            ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, b[j].y, ci[i][j], 0, 0, 0);
-            cs[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x + a[i].y, b[j].x + b[j].y, cs[i][j], 0, 0, 0);
-          }
-      } else {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int j = 0; j < NB; ++j) {
-            cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, cr[i][j], 0, 0, 0);
-            ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].y, ci[i][j], 0, 0, 0);
-          }
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int j = 0; j < NB; ++j) {
-            cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, nbi[j], cr[i][j], 0, 0, 0);
-            ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, b[j].x, ci[i][j], 0, 0, 0);
-          }
-      }
-    }
-    if (kt + 1 < nk) {
-      la.template store<AS>(As[cur ^ 1], t);
-      lb.template store<BS>(Bs[cur ^ 1], t);
-    }
-    __syncthreads();
+        for (int r = 0; r < 4; ++r) {
+          const int row = m0 + wm * WTM + i * 16 + (MF4 ? 4 * r + (lane >> 4) : (lane >> 4) + 4 * r);
+          const int col = n0 + wn * WTN + j * 16 + (lane & 15);
+          if (row < M && col < N) old[kEarlyC ? i : 0][kEarlyC ? j : 0][r] = pr.C[(int64_t)row * pr.ldc + col];
+        }
   }
+  __syncthreads();
+  // (a branch that the whole workgroup takes: there are barriers inside)
+  auto run = [&](auto all) {   // all: every block has outputs
+    for (int kt = 0; kt < nk; ++kt) {
+      const int cur = kt & 1;
+      if (kt + 1 < nk) {
+        la.load(pr.A, pr.lda, m0, (kt + 1) * BK, M, K, OPA == OP_C, t);
+        lb.load(pr.B, pr.ldb, n0, (kt + 1) * BK, N, K, OPB == OP_C, t);
+      }
+      const double2* __restrict__ as = As[cur];
+      const double2* __restrict__ bs = Bs[cur];
+      auto step = [&](int kk) {
+        const int k = kk * 4 + (lane >> 4);
+        if (MF4) {
+          double2 b[NB], a4[MB][4];
+#pragma unroll
+          for (int j = 0; j < NB; ++j) b[j] = bs[k * BS + wn * WTN + j * 16 + (lane & 15)];
+#pragma unroll
+          for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int I = 0; I < 4; ++I) a4[i][I] = as[k * AS + wm * WTM + i * 16 + 4 * I + (lane & 3)];
+#pragma unroll
+          for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+              for (int I = 0; I < 4; ++I) {
+                if (!all && (i >= mb || j >= nb)) continue;
+                const double2 x = a4[i][I], y = b[j];
+                if (M3) {
+                  cr[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.x, y.x, cr[i][j][I], 0, 0, 0);
+                  ci[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.y, y.y, ci[i][j][I], 0, 0, 0);
+                  cs[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.x + x.y, y.x + y.y, cs[i][j][I], 0, 0, 0);
+                } else {
+                  cr[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.x, y.x, cr[i][j][I], 0, 0, 0);
+                  ci[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.x, y.y, ci[i][j][I], 0, 0, 0);
+                  cr[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.y, -y.y, cr[i][j][I], 0, 0, 0);
+                  ci[i][j][I] = __builtin_amdgcn_mfma_f64_4x4x4f64(x.y, y.x, ci[i][j][I], 0, 0, 0);
+                }
+              }
+          return;
+        }
+        double2 a[MB], b[NB];
+        double nbi[NB];
+#pragma unroll
+        for (int i = 0; i < MB; ++i) a[i] = as[k * AS + wm * WTM + i * 16 + (lane & 15)];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          b[j] = bs[k * BS + wn * WTN + j * 16 + (lane & 15)];
+          nbi[j] = -b[j].y;
+        }
+        if (M3) {
+          // cr = T1 (Ar Br), ci = T2 (Ai Bi), cs = T3 ((Ar + Ai)(Br + Bi))
+#pragma unroll
+          for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+              if (!all && (i >= mb || j >= nb)) continue;
+              cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, cr[i][j], 0, 0, 0);
+              ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, b[j].y, ci[i][j], 0, 0, 0);
+              cs[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x + a[i].y, b[j].x + b[j].y, cs[i][j], 0, 0, 0);
+            }
+        } else {
+#pragma unroll
+          for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+              if (!all && (i >= mb || j >= nb)) continue;
+              cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, cr[i][j], 0, 0, 0);
+              ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].y, ci[i][j], 0, 0, 0);
+            }
+#pragma unroll
+          for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+              if (!all && (i >= mb || j >= nb)) continue;
+              cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, nbi[j], cr[i][j], 0, 0, 0);
+              ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, b[j].x, ci[i][j], 0, 0, 0);
+            }
+        }
+      };
+      if (all || (mb > 0 && nb > 0)) {
+#pragma unroll
+        for (int kk = 0; kk < BK / 4; ++kk) step(kk);
+      }
+      if (kt + 1 < nk) {
+        la.template store<AS>(As[cur ^ 1], t);
+        lb.template store<BS>(Bs[cur ^ 1], t);
+      }
+      __syncthreads();
+    }
+  };
+  if (edge) run(std::false_type{});
+  else run(std::true_type{});
 
   // epilogue: D = alpha * acc + beta * C
 #pragma unroll
@@ -245,7 +285,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_zgemm(const GemmProb* __rest
           }
           double2 o = make_double2(alpha_re * xr - alpha_im * xi, alpha_re * xi + alpha_im * xr);
           if (beta) {
-            const double2 c = pr.C[(int64_t)row * pr.ldc + col];
+            const double2 c = kEarlyC ? old[kEarlyC ? i : 0][kEarlyC ? j : 0][r] : pr.C[(int64_t)row * pr.ldc + col];
             o.x += c.x;
             o.y += c.y;
           }
