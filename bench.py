@@ -8,7 +8,7 @@ with planar separators, leaves <= 8 sites per side.  The fold and the
 extraction run in double-double (precision 2 and 3: the settings whose results
 agree with the oracle to 1e-10 at every energy of the grid, out of the lead
 band included); with precision 3, the default, every double-double block
-product of depth >= 32 is formed from 8-bit slices on the integer matrix
+product of depth >= 32 is formed from int8 residues on the integer matrix
 cores.
 
 One step = diag G^r, diag G^< and T for one batch of energies (16 by default),
@@ -42,13 +42,16 @@ FP64_VALU_PEAK_TOPS = 39.3
 DD_OPS_PER_CMAC = 36
 DD_OPS_PER_CFLOP = DD_OPS_PER_CMAC / 8
 # dense int8 matrix-core peak of the chip (5.0 P int8 ops/s) and the int8 operations of one complex
-# double-double multiply-add in k_oz_gemm: 3 real products (Gauss) x S (S + 1) / 2 slice pairs
-# (s + t <= S - 1) x 2; S = 16 slices per operand unless --slices 15
+# double-double multiply-add in k_oz_gemm: two real products for 18 of its 32 moduli and four for 14 (92)
+# x 2, for 16 digits of 7 bits per operand as for 15
 INT8_MFMA_PEAK_TOPS = 5000.0
+OZ_RESIDUE_OPS_PER_CMAC = (18 * 2 + 14 * 4) * 2
 OZ_DEFAULT_SLICES = 16
 
 
 def oz_int8_ops_per_cmac(slices):
+    """The same multiply-add from slice pairs s + t <= S - 1 of S slices, three real products (Gauss): what the
+    residues replace."""
     s = slices or OZ_DEFAULT_SLICES
     return 3 * (s * (s + 1) // 2) * 2
 
@@ -66,8 +69,8 @@ OZ_TRAFFIC = {"sources": ["paper_1702_05167_amd/csrc/ozaki.hip", "paper_1702_051
 
 
 def oz_sources_sha256():
-    """SHA-256 over what defines k_oz_gemm: the slice-product section of ozaki.hip (its staging, matrix-core
-    loop, epilogue sums and the kernel) and the slice-count lines of kern.h."""
+    """SHA-256 over what defines k_oz_gemm: the product section of ozaki.hip (its staging, matrix-core
+    loop, epilogue sums and the kernel) and the digit-count lines of kern.h."""
     import hashlib
     h = hashlib.sha256()
     for rel in OZ_TRAFFIC["sources"]:
@@ -78,7 +81,7 @@ def oz_sources_sha256():
         if rel.endswith("kern.h"):
             data = b"".join(line for line in data.splitlines(keepends=True) if b"constexpr int kOzSlices" in line)
         else:
-            a, b = data.find(b"// products of the slices"), data.find(b"// the allocation-free product")
+            a, b = data.find(b"// products of the residues"), data.find(b"// the allocation-free product")
             if a < 0 or b < a:
                 return None
             data = data[a:b]
@@ -126,19 +129,21 @@ def golden_errors(np, gold, gr_all, gl_all, tr_all):
             "out_of_band_max": max(x for x, b in zip(errs, band) if not b)}
 
 
-def roofline_of(prof, precision, prof_bytes=None, slices=0):
+def roofline_of(prof, precision, prof_bytes=None, slices=0, int8_ops=None):
     """Algorithmic roofline of the dominant block-product kernel from per-kind launch timing
     (HIP events on the solver's stream): achieved = sum of 8 M N K over its launches / sum of
-    their durations, against the FP64 matrix-core peak."""
+    their durations, against the FP64 matrix-core peak.  int8_ops: int8 operations of one complex
+    multiply-add as executed (default: the slice pairs')."""
     total_ms = sum(v["ms"] for v in prof.values())
     g, gd, go = prof["gemm"], prof["dd_gemm"], prof["oz_gemm"]
     if go["ms"] > max(gd["ms"], g["ms"]):
         ach = go["flops"] / (go["ms"] * 1e-3) / 1e12
-        i8 = ach * oz_int8_ops_per_cmac(slices) / 8
+        ops = int8_ops or oz_int8_ops_per_cmac(slices)
+        i8 = ach * ops / 8
         alg_bytes = prof_bytes["oz_gemm"] / go["launches"] if prof_bytes and go["launches"] else None
-        # the counters were taken with the default slice count
+        # the counters were taken with the default digit count
         traffic = oz_traffic() if (slices or OZ_DEFAULT_SLICES) == OZ_DEFAULT_SLICES else None
-        return {"bound": "mfma", "kernel": "k_oz_gemm (complex double-double products from 8-bit slices, "
+        return {"bound": "mfma", "kernel": "k_oz_gemm (complex double-double products from int8 residues, "
                                            "integer matrix cores)",
                 "achieved": ach, "peak": FP64_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": ach / FP64_MFMA_PEAK_TFLOPS,
                 "traffic": traffic, "flop_count": "8 M N K per complex product (algorithmic)",
@@ -149,8 +154,8 @@ def roofline_of(prof, precision, prof_bytes=None, slices=0):
                 "share_of_kernel_time": go["ms"] / total_ms,
                 "int8_matrix_cores": {"achieved": i8, "peak": INT8_MFMA_PEAK_TOPS, "unit": "T int8 ops/s",
                                       "frac": i8 / INT8_MFMA_PEAK_TOPS,
-                                      "int8_ops_per_complex_multiply_add": oz_int8_ops_per_cmac(slices),
-                                      "note": "unpadded M N K; padding to 32 x 32 x 64 tiles not counted"}}
+                                      "int8_ops_per_complex_multiply_add": ops,
+                                      "note": "unpadded M N K; padding to 64 x 32 x 64 tiles not counted"}}
     if precision >= 1 and gd["ms"] > 0:
         ach = gd["flops"] / (gd["ms"] * 1e-3) / 1e12
         issue = DD_OPS_PER_CFLOP * ach
@@ -189,14 +194,14 @@ def main():
     ap.add_argument("--no-golden", action="store_true", help="skip the error against stored oracle values")
     ap.add_argument("--precision", type=int, default=3,
                     help="3 (default): fold and extraction in double-double, block products of depth >= 32 from "
-                         "8-bit slices on the integer matrix cores; 2: the same on the FP64 vector units; "
+                         "int8 residues on the integer matrix cores; 2: the same on the FP64 vector units; "
                          "1: double-double fold only; 0: complex128 as in Algorithms 1 and 2")
     ap.add_argument("--leaf", type=int, default=8)
     ap.add_argument("--transverse", action="store_true",
                     help="never cut the transport axis (clusters span contact to contact)")
     ap.add_argument("--tune", type=int, default=1, help="1 (default): autotune the GEMM tile shape per launch")
     ap.add_argument("--slices", type=int, default=0,
-                    help="8-bit slices per operand of the precision-3 products: 0 (the library's 16) or 15")
+                    help="7-bit digits per operand of the precision-3 products: 0 (the library's 16) or 15")
     ap.add_argument("--complex3m", type=int, default=1,
                     help="1 (default): three real products per complex multiply-add in every complex128 block "
                          "product; 0: four")
@@ -338,7 +343,7 @@ def main():
     prof_bytes = ctx.profile_bytes()
     launches = ctx.profile_launches()
     ctx.profile(False)
-    roof = roofline_of(prof, args.precision, prof_bytes, args.slices)
+    roof = roofline_of(prof, args.precision, prof_bytes, args.slices, OZ_RESIDUE_OPS_PER_CMAC)
     by_phase = {}
     for kind, fl, ms, ph in launches:
         key = f"{ctx.PROFILE_PHASES[int(ph)]}/{ctx.PROFILE_KINDS[int(kind)]}"
@@ -434,8 +439,8 @@ def main():
 
     prec_name = {0: "complex128", 1: "double-double fold, complex128 extraction",
                  2: "double-double fold and extraction",
-                 3: f"double-double fold and extraction, products of depth >= 32 from 8-bit slices "
-                    f"({args.slices or OZ_DEFAULT_SLICES} per operand) on the integer matrix cores"}[args.precision]
+                 3: f"double-double fold and extraction, products of depth >= 32 from int8 residues "
+                    f"({args.slices or OZ_DEFAULT_SLICES} 7-bit digits per operand) on the integer matrix cores"}[args.precision]
     line = {
         "metric": "energies/s (diag G^r,G^<), 32^3 cube, batched vs plain; % FP64 MFMA peak",
         "value": value,

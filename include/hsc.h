@@ -144,15 +144,16 @@ typedef struct {
    *     channels and their products is carried in double-double and only the
    *     returned diagonals are rounded to complex128;
    * 3 = as 2, with every double-double block product of depth K >= 32 formed
-   *     on the integer matrix cores: each operand is split into 16 signed
-   *     8-bit slices (`slices` below) scaled by a power of two per row (per
-   *     column of the right operand), to 2^-112 of the row's largest entry,
-   *     the slice products are summed exactly in 32-bit integers, and the pairs
-   *     whose weight is within 2^-105 of the leading one are combined in
-   *     double-double (at most about K 2^-104 times the product of the largest
-   *     row and column entries; products with K < 32, the
-   *     pivot-block inverse updates among them, stay on the vector units).
-   *     Needs a slice scratch of up to 4 GiB besides the workspace.
+   *     on the integer matrix cores, where that is estimated to pay: each
+   *     operand is rounded to integers of 16 digits of 7 bits (`slices` below)
+   *     times a power of two per row (per column of the right operand), to
+   *     2^-112 of the row's largest entry, and the integers' product is formed
+   *     exactly from its residues modulo 32 small numbers, whose products are
+   *     summed in 32-bit integers, by the Chinese remainder theorem (at most
+   *     about K 2^-109 times the product of the largest row and column entries,
+   *     rounded to double-double; products with K < 32, the rank-8 updates of
+   *     the pivot-block inverses among them, stay on the vector units).
+   *     Needs a residue scratch of up to 4 GiB besides the workspace.
    * The unpivoted cluster elimination amplifies rounding errors by up to
    * ~1/sigma_min(A_ii)^2 at energies where a cluster block A_ii is nearly
    * singular (outside the lead band, where nothing broadens it): in the fold
@@ -171,20 +172,21 @@ typedef struct {
    * of its launches and keep the fastest per launch; 0: 64x64 everywhere.  With
    * complex3m = 1 the candidates are the three-product kernels plus the 128x128
    * four-product one.  Double-double products (precision >= 1) are timed with
-   * 32x32, 64x32 and 64x64 tiles (untuned: 64x32).  Results agree to rounding. */
+   * 32x32, 64x32, 64x64 and 16x16 tiles (untuned: the largest of 64x32 and 32x32
+   * that gives every CU two workgroups, else 16x16).  Results agree to rounding. */
   int32_t tune;
   /* Complex block products: 0 = four real products per complex multiply-add
    * (Re = ArBr - AiBi, Im = ArBi + AiBr); 1 = three (Gauss: ArBr, AiBi,
    * (Ar+Ai)(Br+Bi)), a quarter less matrix-core work with an imaginary-part
    * error bound proportional to (|Ar| + |Ai|)(|Br| + |Bi|). */
   int32_t complex3m;
-  /* precision 3: 8-bit slices per operand of the integer-matrix-core products.
+  /* precision 3: 7-bit digits per operand of the integer-matrix-core products.
    * 0 = 16 (the default), or 16 or 15: fifteen keep every operand to 2^-105
    * instead of 2^-112 of its row's largest entry (a product bound of about
-   * K 2^-97 instead of K 2^-104 times the row and column maxima) for 120
-   * instead of 136 slice pairs, about 6 % less solve time; entries far below
-   * their row's largest (large devices out of the lead band) then lose up to
-   * two more digits.  Ignored with precision 0-2.  Other values: HSC_E_ARG. */
+   * K 2^-102 instead of K 2^-109 times the row and column maxima), at the same
+   * cost; entries far below their row's largest (large devices out of the lead
+   * band) then lose up to two more digits.  Ignored with precision 0-2.  Other
+   * values: HSC_E_ARG. */
   int32_t slices;
   /* On-site potential energy U (device, double[n], site order of the tree's H),
    * or NULL: the device Hamiltonian becomes H + diag(U) (the electrostatic
@@ -425,18 +427,20 @@ hsc_status hsc_scf(hsc_ctx* ctx, const hsc_tree* tree, const hsc_grid* grid, int
  * 0 assemble, 1 inverse panel, 2 inverse swap, 3 inverse unscramble, 4 GEMM,
  * 5 gather, 6 N assembly, 7 diagonal output, 8 growth indicators, 9-13 the
  * double-double assemble / panel / swap / unscramble / GEMM, 14 inverse
- * super-panel preparation, 15 operand splitting into 8-bit slices, 16 slice
+ * super-panel preparation, 15 operand splitting into residues, 16 residue
  * products on the integer matrix cores (precision 3), 17 double-double inverse
  * super-panel preparation, 18-19 the dense self-energy of whole-face contacts
- * (partial mode sums, then the face block), 20 bond entries (HSC_BOND_GR/GL).
+ * (partial mode sums, then the face block), 20 bond entries (HSC_BOND_GR/GL),
+ * 21 the double-double inverses' rank-8 updates inside a super-panel.  Kind 11
+ * has no launches: the double-double inverse interchanges no rows.
  * hsc_ctx_profile_read writes out[3*k + {0,1,2}] = launches, milliseconds,
  * algorithmic real flops (GEMM: 8 M N K per problem) for k < n_kinds.
  * Errors: HSC_E_ARG. */
 hsc_status hsc_ctx_profile(hsc_ctx* ctx, int32_t enable);
 hsc_status hsc_ctx_profile_read(hsc_ctx* ctx, double* out, int32_t n_kinds);
 /* out[k] = algorithmic bytes of the timed launches of kind k since profiling was enabled (so far
- * counted for the slice products, kind 16: slices of both operands read, 3 S B per complex
- * element with S slices per operand; row and column scales; the double-double result written, its rounded copy, and C when
+ * counted for the residue products, kind 16: residues of both operands read, 64 B per complex
+ * element; row and column scales; the double-double result written, its rounded copy, and C when
  * accumulating); 0 for kinds not counted.  Errors: HSC_E_ARG. */
 hsc_status hsc_ctx_profile_bytes(hsc_ctx* ctx, double* out, int32_t n_kinds);
 

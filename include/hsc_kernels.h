@@ -49,13 +49,13 @@ hsc_status hsc_kern_zgemm_tile(hsc_ctx* ctx, int32_t tile_kind, int32_t opA, int
  * result is accurate to about 2^-104 relative to sum_k |op(A)_ik| |op(B)_kj|
  * (products accumulated lazily, renormalised every 8 terms).  config 3: the
  * integer matrix cores (the products of hsc_solve_opts.precision = 3): op(A)
- * split into 16 signed 8-bit slices per element with one power-of-two scale per
- * row, op(B) likewise per column (the error-free splitting of Ozaki et al.),
- * exact int32 sums of slice products, the leading 136 of 256 slice pairs
- * combined in double-double; the error is at most about K 2^-104 max_k
+ * rounded to integers of 16 digits of 7 bits with one power-of-two scale per
+ * row, op(B) likewise per column, their product formed exactly from its
+ * residues modulo 32 small numbers (int8 products summed in int32) by the
+ * Chinese remainder theorem; the error is at most about K 2^-109 max_k
  * (|Re| + |Im|) of row i of op(A) times the same of column j of op(B), plus
- * 2^-104 |C_ij|, K <= 10880.  config 4: as 3 with 15 slices (120 pairs, the
- * products of hsc_solve_opts.slices = 15): K 2^-97 instead of K 2^-104,
+ * 2^-104 of the result and of |C_ij|, K <= 10880.  config 4: as 3 with 15 digits
+ * (the products of hsc_solve_opts.slices = 15): K 2^-102 instead of K 2^-109,
  * K <= 11648.  beta is 0 or 1; C
  * may equal D and may be NULL when beta = 0.  Synchronous.
  * Errors: HSC_E_ARG (sizes < 0, bad op or config, leading dimension too small,
@@ -66,15 +66,16 @@ hsc_status hsc_kern_zgemm_dd(hsc_ctx* ctx, int32_t config, int32_t opA, int32_t 
 
 /* For callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): the double-double
- * product of hsc_kern_zgemm_dd with config 3 (8-bit slices on the integer
+ * product of hsc_kern_zgemm_dd with config 3 (int8 residues on the integer
  * matrix cores), same arguments, same kernels, same results, with every
- * descriptor, slice plane and scale in one static device array of 64 MiB per
+ * descriptor, residue plane and scale in one static device array of 86 MiB per
  * GPU (held from the first context on that GPU until the process ends); the
- * call allocates nothing and does not wait: it enqueues four kernels on the
+ * call allocates nothing and does not wait: it enqueues three kernels on the
  * context's stream and returns (D is valid after hsc_sync or a stream
- * synchronisation).  Limit: the scratch of one product, 48 (Mp + Np) Kp bytes
- * plus maps (Mp, Np = M, N rounded up to 32, Kp = K rounded up to 64), must fit
- * 64 MiB (e.g. M = N = 1024 with K <= 640); larger products return HSC_E_ARG.
+ * synchronisation).  Limit: 48 (Mp + Np) Kp bytes plus maps (Mp, Np = M, N
+ * rounded up to 32, Kp = K rounded up to 64) must not exceed 64 MiB (e.g. M = N =
+ * 1024 with K <= 640); larger products return HSC_E_ARG.  (The residues take 64
+ * bytes instead of 48 and the array holds them for every product accepted.)
  * Every call on one GPU shares that array and leaves it holding its own
  * intermediates: calls that overlap on one GPU (other streams, other contexts,
  * other threads) race and must be serialised by the caller.

@@ -58,7 +58,7 @@ struct Blob {
   }
   // mark a pointer field (at byte offset `field`) as holding a blob offset
   void reloc(size_t field) { relocs.push_back(field); }
-  // pointer fields holding offsets into the plan's slice scratch (double-double products on the
+  // pointer fields holding offsets into the plan's residue scratch (double-double products on the
   // integer matrix cores), rebased when the scratch is allocated
   std::vector<size_t> sc_relocs;
 };
@@ -89,7 +89,7 @@ struct Step {
   int out = 0;                // DIAG destination
   int dd = 0;                 // row kernels: operands in double-double
   double flops = 0;           // algorithmic real flops of this launch (GEMM: 8 M N K)
-  double bytes = 0;           // algorithmic bytes of this launch (slice products: operands read, result written)
+  double bytes = 0;           // algorithmic bytes of this launch (residue products: operands read, result written)
   int phase = 0;              // part of the method (Phase), for launch timing
 };
 
@@ -120,7 +120,7 @@ struct Plan {
   int prec = 0;
   int tune = 0;
   int m3 = 0;                    // complex products in the three-multiplication form
-  int slices = kOzSlices;        // 8-bit slices per operand of the products on the integer matrix cores
+  int slices = kOzSlices;        // 7-bit digits per operand of the products on the integer matrix cores
   int inst = 0;                  // instance of this shape (one per stream of a call with concurrent batches)
   int64_t n = 0;
   char* ws = nullptr;
@@ -138,7 +138,7 @@ struct Plan {
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
   char* stage = nullptr;
-  char* oz = nullptr;            // slice scratch of the products on the integer matrix cores
+  char* oz = nullptr;            // residue scratch of the products on the integer matrix cores
   size_t oz_bytes = 0;
   const FaceTransJob* face_tj = nullptr;   // [B] transmission over the left face (whole-face contacts)
   double* pot = nullptr;          // [n] on-site potential in cluster order (workspace)
@@ -199,9 +199,9 @@ struct Builder {
   bool gl;        // any lesser output -> full ancestor rows on contact paths
   bool ddf = false;   // double-double fold
   bool ddx = false;   // double-double extraction as well (G, the lesser channels)
-  bool oz = false;    // double-double products from 8-bit slices on the integer matrix cores
-  int slices = kOzSlices;   // slices per operand of those products
-  size_t oz_need = 0; // largest slice scratch of one such product step
+  bool oz = false;    // double-double products from int8 residues on the integer matrix cores
+  int slices = kOzSlices;   // digits per operand of those products
+  size_t oz_need = 0; // largest residue scratch of one such product step
   size_t ws = 0;  // workspace bytes
   Blob blob;
   std::vector<Step> steps;
@@ -222,7 +222,7 @@ struct Builder {
     size_t Fd, Invd, Psid, Td, Rd;   // double-double fold
     size_t NF[kMaxChannels], NFc[kMaxChannels], M[kMaxChannels], PX[kMaxChannels], PFF[kMaxChannels],
         PT[kMaxChannels];
-    // 8-bit slices of operands used by several products (precision 3): Psi (rows n, depth f),
+    // residues of operands used by several products (precision 3): Psi (rows n, depth f),
     // Psi^T and A_ii^-1 of separators (rows f / n, depth n); 0 = none
     size_t PsiS, PsiTS, InvS;
   };
@@ -508,7 +508,7 @@ struct Builder {
   // ---- step helpers ----
   template <class T> struct GPT {
     const T *A, *B, *C; T* D; int M, N, K, lda, ldb, ldc, ldd;
-    size_t sa = 0;   // workspace offset of op(A)'s slices when they are kept for other products (0: none)
+    size_t sa = 0;   // workspace offset of op(A)'s residues when they are kept for other products (0: none)
   };
   using GP = GPT<double2>;
   void gemm(int opA, int opB, const std::vector<GP>& ps, double ar, double ai, int beta) {
@@ -620,17 +620,17 @@ struct Builder {
 
   struct GPD {
     const zdd *A, *B, *C; zdd* D; double2* D64; int M, N, K, lda, ldb, ldc, ldd, ldd64;
-    size_t sa = 0;   // workspace offset of op(A)'s kept slices (0: split into the step's scratch)
+    size_t sa = 0;   // workspace offset of op(A)'s kept residues (0: split into the step's scratch)
     // Gauss-Jordan update (matrix cores): A minus the identity at the rows piv[k], B's row k is piv[k]
     const int32_t* piv = nullptr;
   };
-  std::vector<size_t> oz_kept;   // kept slice buffers already split by an earlier step
+  std::vector<size_t> oz_kept;   // kept residue buffers already split by an earlier step
   // Double-double block products: with `oz`, every problem whose depth K lies in
-  // [kOzMinK, kOzMaxK] and whose estimated time (splitting + slice product) beats the vector units
+  // [kOzMinK, kOzMaxK] and whose estimated time (splitting + residue product) beats the vector units
   // runs on the integer matrix cores; the others, and every product without `oz`, on the FP64
   // vector units.
   static constexpr int kOzMinK = 32;
-  static constexpr size_t kOzStepCap = size_t(4) << 30;   // slice scratch of one product step
+  static constexpr size_t kOzStepCap = size_t(4) << 30;   // residue scratch of one product step
   // Measured costs on the target (seconds): splitting one complex double-double element into
   // residues, one padded multiply-add and one output of the residue product, one multiply-add on the
   // vector units (1.5 ps in full tiles, 2.2-3.6 ps in the products of small trees).  A forest of 8 devices
@@ -657,7 +657,7 @@ struct Builder {
     return oz_round((size_t)kOzPlanes * oz_rows(R) * oz_round(K, 64) + 4 * (size_t)oz_rows(R), 256);
   }
 
-  // split + product steps, the problem list cut into pieces whose slices fit kOzStepCap; an operand
+  // split + product steps, the problem list cut into pieces whose residues fit kOzStepCap; an operand
   // shared by several problems of a piece is split once
   void oz_gemm(int opA, int opB, const std::vector<GPD>& ps, int negate, int beta) {
     size_t i0 = 0;
@@ -669,7 +669,7 @@ struct Builder {
       std::map<std::tuple<const void*, int64_t, int64_t, int, int>, std::pair<size_t, size_t>> seen;
       size_t cur = 0, i = i0;
       double flops = 0, bytes = 0;
-      // slices of one operand: in the step's scratch (offsets rebased later, `kept` false) or in a
+      // residues of one operand: in the step's scratch (offsets rebased later, `kept` false) or in a
       // workspace buffer kept for later products (absolute addresses, split by the first step using it)
       std::vector<char> kept_job;   // per split job: writes a kept buffer
       auto operand = [&](const zdd* X, int64_t ldr, int64_t ldk, int R, int K, size_t keep, const int32_t* piv,
@@ -701,7 +701,7 @@ struct Builder {
         seen[key] = r;
         return r;
       };
-      std::vector<char> kept_a;   // per product: A's slices in a kept buffer
+      std::vector<char> kept_a;   // per product: A's residues in a kept buffer
       for (; i < ps.size(); ++i) {
         const GPD& g = ps[i];
         if (g.M <= 0 || g.N <= 0) continue;
@@ -1743,14 +1743,14 @@ hsc_status tune_plan(hsc_ctx* ctx, Plan* pl) {
   return rc;
 }
 
-// Allocate the slice scratch, rebase the blob's pointer fields, upload it and take the steps.
+// Allocate the residue scratch, rebase the blob's pointer fields, upload it and take the steps.
 hsc_status upload_plan(Builder& b, Plan* pl) {
   if (b.oz_need > 0) {
     pl->oz_bytes = b.oz_need;
     if (hipMalloc(&pl->oz, pl->oz_bytes) != hipSuccess) {
       (void)hipGetLastError();
       pl->oz = nullptr;
-      set_error("slice scratch allocation failed (" + std::to_string(pl->oz_bytes) + " bytes)");
+      set_error("residue scratch allocation failed (" + std::to_string(pl->oz_bytes) + " bytes)");
       return HSC_E_OOM;
     }
     for (size_t f : b.blob.sc_relocs) {
@@ -1782,7 +1782,7 @@ hsc_status upload_plan(Builder& b, Plan* pl) {
   return HSC_OK;
 }
 
-// slices: 8-bit slices per operand of the integer-matrix-core products (precision 3), kOzSlices
+// slices: 7-bit digits per operand of the integer-matrix-core products (precision 3), kOzSlices
 // for the other precisions
 // Plan of this shape and instance (a call with concurrent batches holds instances 0 .. inst - 1 of
 // the shape while it builds instance inst: nothing here frees those).
@@ -1882,7 +1882,7 @@ int build_plan(hsc_ctx* ctx, const hsc_tree* t, int B, uint32_t want, int prec, 
   {
     hsc_status rc = upload_plan(b, pl.get());
     if (rc == HSC_E_OOM && b.oz_need > 0 && !pl->oz && !ctx->plans.empty()) {
-      // the slice scratch did not fit beside the cached plans (nothing of this plan was uploaded
+      // the residue scratch did not fit beside the cached plans (nothing of this plan was uploaded
       // yet): drop the ones this call does not hold and try once more
       drop_unheld();
       rc = upload_plan(b, pl.get());
@@ -1997,7 +1997,7 @@ hsc_status hsc_ctx_destroy(hsc_ctx* ctx) {
   return HSC_OK;
 }
 
-// slices per operand of a solve's integer-matrix-core products: the option (0 = kOzSlices) with
+// digits per operand of a solve's integer-matrix-core products: the option (0 = kOzSlices) with
 // precision 3, kOzSlices otherwise (no such products); -1 when the option is out of range
 static int opts_slices(const hsc_solve_opts* o) {
   if (o->slices != 0 && (o->slices < kOzSlicesMin || o->slices > kOzSlicesMax)) return -1;
@@ -2695,7 +2695,7 @@ namespace {
 
 size_t oz_pad(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// one product on the integer matrix cores (split A', split B', slice product), synchronous
+// one product on the integer matrix cores (split A', split B', residue product), synchronous
 hsc_status kern_zgemm_oz(hsc_ctx* ctx, int slices, int opA, int opB, int M, int N, int K, int negate, const void* A,
                          int lda, const void* B, int ldb, int beta, const void* C, int ldc, void* D, int ldd) {
   const int Mp = oz_rows(M), Np = oz_rows(N), Kp = (int)oz_pad(K, 64);
@@ -2805,7 +2805,7 @@ hsc_status hsc_kern_zgemm_tile(hsc_ctx* ctx, int32_t tile_kind, int32_t opA, int
 hsc_status hsc_kern_zgemm_dd(hsc_ctx* ctx, int32_t config, int32_t opA, int32_t opB, int32_t M, int32_t N,
                              int32_t K, int32_t negate, const void* A, int32_t lda, const void* B, int32_t ldb,
                              int32_t beta, const void* C, int32_t ldc, void* D, int32_t ldd) {
-  // configs past the vector-unit tiles: the slice product with 16 slices (3) or 15 (4)
+  // configs past the vector-unit tiles: the residue product with 16 digits (3) or 15 (4)
   const int oz_slices = config == kDDPublicConfigs ? 16 : config == kDDPublicConfigs + 1 ? 15 : 0;
   if (!ctx || M < 0 || N < 0 || K < 0 || opA < 0 || opA > 1 || opB < 0 || opB > 1 || (beta != 0 && beta != 1) ||
       (negate != 0 && negate != 1) || config < 0 || config > kDDPublicConfigs + 1 ||

@@ -176,7 +176,7 @@ class Context:
                      "face_half", "face_sigma", "bonds", "dd_inv_rank")
 
     def profile_bytes(self) -> dict:
-        """Algorithmic bytes per launch kind since profiling was enabled (slice products only)."""
+        """Algorithmic bytes per launch kind since profiling was enabled (residue products only)."""
         k = len(self.PROFILE_KINDS)
         buf = np.zeros(k)
         check(lib().hsc_ctx_profile_bytes(self.h, _ptr(buf), k))
@@ -348,7 +348,7 @@ def solve(ctx: Context, tree: Tree, energies, eta=1e-8, kT=0.025, mu_L=0.1, mu_R
           guard_tau=0.0, guard_rounds=6, precision=3, graph=0, tune=0, complex3m=0, slices=0, potential=None,
           streams=0):
     """Solve all energies; returns a dict of device tensors (gr, gl, trans, spectral, status).
-    slices: 8-bit slices per operand of the precision-3 products (0 = the library's 16, or 15).
+    slices: 7-bit digits per operand of the precision-3 products (0 = the library's 16, or 15).
     potential: device float64 [n] on-site potential energy added to H (site order), or None.
     streams: batches run round-robin on that many streams at once (each with its own plan), 0 or 1
     one after another."""
@@ -532,8 +532,8 @@ def kern_zgemm(ctx, opA, opB, alpha, A, B, beta=0, C_=None, D=None, tile=0):
 def kern_zgemm_dd(ctx, opA, opB, A, B, negate=0, beta=0, C_=None, D=None, config=0):
     """D = (-1)^negate op(A) op(B) + beta C in complex double-double.  A, B, C, D: device float64
     tensors of shape (rows, cols, 4) holding (re hi, re lo, im hi, im lo) per element.  config 0-2:
-    tiles of the FP64 vector-unit kernel; 3: 16 8-bit slices per operand on the integer matrix cores;
-    4: 15 slices."""
+    tiles of the FP64 vector-unit kernel; 3: int8 residues on the integer matrix cores, operands of 16
+    digits of 7 bits; 4: of 15."""
     import torch
     M = A.shape[0] if opA == 0 else A.shape[1]
     K = A.shape[1] if opA == 0 else A.shape[0]
