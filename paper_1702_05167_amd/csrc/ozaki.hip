@@ -60,6 +60,19 @@ __device__ __forceinline__ int res_byte(int c, int p, float inv) {
   return c + __mul24(q, -p);
 }
 
+// The same for sums that start from a bias (the accumulators' initial value) instead of zero: the bits of
+// the float M + c, M the multiple of p nearest to 1.5 2^23 that is also one of 256, so that the sum needs no conversion
+// and its low byte is c's.  |c| < 2^21 keeps M + c inside the float's binade; (M + c) / p misses by at
+// most 0.8 / p, so the residue stays within (p + 2) / 2.
+constexpr int kResBias = 12582912;
+constexpr int res_bias(int p) { return p == 256 ? kResBias : (kResBias + 128 * p) / (256 * p) * (256 * p); }
+constexpr int res_bias_bits(int p) { return 0x4b000000 + res_bias(p) - 8388608; }
+__device__ __forceinline__ int res_byte_biased(int s, int p, float inv) {
+  if (p == 256) return s;
+  const int q = __float_as_int(fmaf(__int_as_float(s), inv, (float)(kResBias - res_bias(p) / p)));
+  return s + __mul24(q, -p);
+}
+
 // low bytes of four residues in one word
 __device__ __forceinline__ uint32_t res_pack(int a, int b, int c, int d) {
   const uint32_t ab = __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x0c0c0400);
@@ -111,8 +124,11 @@ __device__ __forceinline__ v4i oz_chunks(dd y) {
 // diagonal over the four k groups of the operand, times the lane's own 16 bytes give each lane its own
 // four sums, at a quarter of the matrix rate but four times that of dot products on the vector units.
 //
-// Bound by memory: 32 B read, read again from beyond L2, and 64 B written per complex element.
-__global__ __launch_bounds__(256) void k_oz_split(const OzSplitJob* __restrict__ jobs,
+// Bound by memory: 32 B read, read again from beyond L2, and 64 B written per complex element, 26-30 ps over the
+// operands of a 16^3 or 32^3 solve (4.9 TB/s), with the four waves per SIMD that the registers allow (28-31 ps
+// with three, accumulators in the other half of the register file and sums converted to float).  Elements
+// held in registers instead of read again take those registers: no faster up to K = 128, slower beyond.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_oz_split(const OzSplitJob* __restrict__ jobs,
                                                   const int32_t* __restrict__ tile_job, int bits) {
   // weights [plane, part][modulus], then as many zeros for the lanes off the block diagonal
   __shared__ v4i wt[2 * 4 * kResMods];
@@ -173,11 +189,13 @@ __global__ __launch_bounds__(256) void k_oz_split(const OzSplitJob* __restrict__
 #pragma unroll
       for (int pl = 0; pl < 2; ++pl) {
         const v4i wr = wl[(2 * pl) * kResMods + 4 * q], wi = wl[(2 * pl + 1) * kResMods + 4 * q];
+        const v4i bias = {res_bias_bits(kResModuli[4 * q]), res_bias_bits(kResModuli[4 * q + 1]),
+                          res_bias_bits(kResModuli[4 * q + 2]), res_bias_bits(kResModuli[4 * q + 3])};
         v4i s[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           // moduli that do not split: plane 0 is Re alone, plane 1 Im alone
-          s[u] = zero;
+          s[u] = bias;
           if (4 * q < kResSplit || pl == 0) s[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wr, cr[u], s[u], 0, 0, 0);
           if (4 * q < kResSplit || pl == 1) s[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wi, ci[u], s[u], 0, 0, 0);
         }
@@ -185,10 +203,12 @@ __global__ __launch_bounds__(256) void k_oz_split(const OzSplitJob* __restrict__
         for (int j = 0; j < 4; ++j) {
           const int m = 4 * q + j, p = kResModuli[m];
           const float inv = 1.0f / (float)p;
-          *reinterpret_cast<uint32_t*>(out + (m >> 1) * slot + (2 * (m & 1) + pl) * 1024) =
-              res_pack(res_byte(s[0][j], p, inv), res_byte(s[1][j], p, inv), res_byte(s[2][j], p, inv),
-                       res_byte(s[3][j], p, inv));
+          *(global_ptr<uint32_t>)(out + (m >> 1) * slot + (2 * (m & 1) + pl) * 1024) =
+              res_pack(res_byte_biased(s[0][j], p, inv), res_byte_biased(s[1][j], p, inv),
+                       res_byte_biased(s[2][j], p, inv), res_byte_biased(s[3][j], p, inv));
         }
+        // (groups of moduli one after the other: interleaved they need 170 registers and two waves per SIMD)
+        if (pl == 1) __builtin_amdgcn_sched_barrier(0);
       }
   }
 }
