@@ -60,13 +60,8 @@ __device__ __forceinline__ int res_byte(int c, int p, float inv) {
   return c + __mul24(q, -p);
 }
 
-// The same for sums that start from a bias (the accumulators' initial value) instead of zero: the bits of
-// the float M + c, M the multiple of p nearest to 1.5 2^23 that is also one of 256, so that the sum needs no conversion
-// and its low byte is c's.  |c| < 2^21 keeps M + c inside the float's binade; (M + c) / p misses by at
-// most 0.8 / p, so the residue stays within (p + 2) / 2.
-constexpr int kResBias = 12582912;
-constexpr int res_bias(int p) { return p == 256 ? kResBias : (kResBias + 128 * p) / (256 * p) * (256 * p); }
-constexpr int res_bias_bits(int p) { return 0x4b000000 + res_bias(p) - 8388608; }
+// The same for sums that start from the bits of the float M = res_bias(p): no conversion.  (M + c) / p misses
+// by at most 0.8 / p, so the residue stays within (p + 2) / 2.
 __device__ __forceinline__ int res_byte_biased(int s, int p, float inv) {
   if (p == 256) return s;
   const int q = __float_as_int(fmaf(__int_as_float(s), inv, (float)(kResBias - res_bias(p) / p)));

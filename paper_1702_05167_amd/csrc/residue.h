@@ -26,6 +26,13 @@ constexpr int kResModuli[kResMods] = {
     241, 233, 229, 221, 205, 197, 193, 181, 173, 157, 149, 137, 113, 109, 101, 97, 89, 73,
     256, 243, 239, 227, 223, 217, 209, 199, 191, 179, 167, 163, 151, 139};
 
+// M, the multiple of 256 p (of 256 for p = 256) nearest to 1.5 2^23, and the bits of the float M: an integer sum
+// c started from them is, read as a float, M + c, without a conversion and with c's low byte, as long as
+// |c| < 2^22 - 2^15 keeps it inside the float's binade (p = 256 takes the byte alone)
+constexpr int kResBias = 12582912;
+constexpr int res_bias(int p) { return p == 256 ? kResBias : (kResBias + 128 * p) / (256 * p) * (256 * p); }
+constexpr int res_bias_bits(int p) { return 0x4b000000 + res_bias(p) - 8388608; }
+
 struct alignas(16) ResTables {
   int32_t p[kResMods];
   float inv[kResMods];

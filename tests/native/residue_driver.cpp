@@ -18,5 +18,9 @@ int main() {
         for (int b = 0; b < 16; ++b) std::printf("%d ", t.crt[part][g][l][b]);
         std::printf("\n");
       }
+  for (int m = 0; m < hsc::kResMods; ++m) std::printf("%d ", hsc::res_bias_bits(t.p[m]));
+  std::printf("\n");
+  for (int m = 0; m < hsc::kResMods; ++m) std::printf("%d ", hsc::kResBias - hsc::res_bias(t.p[m]) / t.p[m]);
+  std::printf("\n");
   return 0;
 }

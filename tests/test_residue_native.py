@@ -6,6 +6,7 @@ import random
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -27,7 +28,7 @@ def tab(tmp_path_factory):
     crt = [[rows[128 + (2 * part + g) * int(nl):128 + (2 * part + g + 1) * int(nl)] for g in range(2)]
            for part in range(2)]
     return dict(p=p, nsplit=int(ns), limbs=int(nl), bits=int(bits), hi=float.fromhex(hi), lo=float.fromhex(lo),
-                split=split, crt=crt)
+                split=split, crt=crt, bias=rows[-2], bias_off=rows[-1])
 
 
 def _chunk_bytes(x):
@@ -114,3 +115,25 @@ def test_products_come_back_exactly(tab, depth):
                 s -= 1 << bits
             # the weights are kept to 2^-160: s / 2^160 = X / P to 32 * 128 * 2^-160
             assert abs(s * P - (want << bits)) <= 4096 * P, (part, want)
+
+
+def test_biased_sums_give_the_same_residues(tab):
+    # sums of one element's digits (32 products of at most 128 x 121) and of products up to 128 deep
+    top = 2 * 128 * 122 ** 2
+    rng = np.random.default_rng(0)
+    c = np.concatenate([np.arange(-3000, 3000), rng.integers(-top, top + 1, 20000), [-top, top]])
+    for p, bias, off in zip(tab["p"], tab["bias"], tab["bias_off"]):
+        bits = (bias + c).astype(np.int32)
+        if p != 256:
+            near = np.concatenate([k * p + np.arange(-2, 3) + p // 2 for k in rng.integers(-top // p + 2, top // p - 2, 400)])
+            bits = np.concatenate([bits, (bias + near).astype(np.int32)])
+        f = bits.view(np.float32)
+        s = bits.astype(np.int64) - bias
+        inv = np.float32(1.0) / np.float32(p)
+        q = (f.astype(np.float64) * np.float64(inv) + off).astype(np.float32).view(np.int32).astype(np.int64)
+        byte = (bits.astype(np.int64) - p * (q & 0xffffff)) & 0xff
+        r = np.where(byte > 127, byte - 256, byte)
+        assert ((r - s) % p == 0).all(), p
+        if p != 256:
+            assert (np.abs(f.astype(np.float64) - 2.0 ** 23 * 1.5) < 2 ** 22).all()
+            assert np.abs(r).max() <= (p + 2) // 2
