@@ -488,7 +488,12 @@ static int ingest(hsc_tree* t, int64_t n, const int64_t* indptr, const int32_t* 
   {
     std::vector<int64_t> ord(nnz);
     for (int64_t r = 0; r < n; ++r) {
-      for (int64_t q = indptr[r]; q < indptr[r + 1]; ++q) ord[q] = q;
+      bool sorted = true;   // (already, without duplicates)
+      for (int64_t q = indptr[r]; q < indptr[r + 1]; ++q) {
+        ord[q] = q;
+        sorted = sorted && (q == indptr[r] || indices[q - 1] < indices[q]);
+      }
+      if (sorted) continue;
       std::sort(ord.begin() + indptr[r], ord.begin() + indptr[r + 1],
                 [&](int64_t a, int64_t b) { return indices[a] < indices[b]; });
     }
@@ -506,7 +511,32 @@ static int ingest(hsc_tree* t, int64_t n, const int64_t* indptr, const int32_t* 
       *re = sr; *im = si;
       return hit;
     };
-    for (int64_t r = 0; r < n; ++r)
+    // Rows in order: the entries (c, r) of a symmetric H come up in the order of row c.  Each row keeps its
+    // place (a search per entry, below, takes twice as long); anything else is left to the search.
+    bool symmetric = true;
+    {
+      std::vector<int64_t> at(indptr, indptr + n);
+      auto sum = [&](int64_t* q, int64_t end, double* re, double* im) {   // the entries of one column
+        const int32_t c = indices[ord[*q]];
+        *re = *im = 0.0;
+        for (; *q < end && indices[ord[*q]] == c; ++*q) {
+          *re += values_ri[2 * ord[*q]];
+          *im += values_ri[2 * ord[*q] + 1];
+        }
+      };
+      for (int64_t r = 0; r < n && symmetric; ++r)
+        for (int64_t q = indptr[r]; q < indptr[r + 1];) {
+          const int32_t c = indices[ord[q]];
+          double ar, ai, br, bi;
+          sum(&q, indptr[r + 1], &ar, &ai);
+          symmetric = at[c] < indptr[c + 1] && indices[ord[at[c]]] == r;
+          if (!symmetric) break;
+          sum(&at[c], indptr[c + 1], &br, &bi);
+          symmetric = ar == br && ai == bi;
+          if (!symmetric) break;
+        }
+    }
+    for (int64_t r = 0; r < n && !symmetric; ++r)
       for (int64_t q = indptr[r]; q < indptr[r + 1]; ++q) {
         int32_t c = indices[q];
         double ar, ai, br, bi;
