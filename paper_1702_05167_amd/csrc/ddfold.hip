@@ -98,9 +98,11 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 // leading 8 mantissa bits (and exponent) of |Re| + |Im|, the first of equals: one 32-bit key per row, one
 // maximum.  Every thread forms the reciprocal itself (no round trip through LDS), and the columns
 // rotate through the registers so that the step's code is a loop body (the current column is P[.][0]).
-// Also written: T (NB x n) = the panel's columns minus the identity at the pivots, as rows, and R (NB x n) =
-// the pivot rows' old values in the other columns of the super-panel (zero in the panel's own and, in both,
-// beyond its nb columns), the factors of its update.
+// Columns are read and written a column at a time, rows side by side, in the T workspace: the finished panel
+// as its first NB rows (zero beyond nb), the next panel's columns in the NB rows after (from its rank update; the
+// first panel of a super-panel comes from X).  Row by row in X every lane touched a line of its own: 39 and 62 us
+// a panel for n = 500 and 1024 (4 matrices) instead of 30 and 48.  Also written: R (NB x n) = the pivot rows' old values
+// in the other columns of the super-panel (zero in the panel's own and beyond its nb columns).
 template <int TH, int RPT, int NB>
 __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_dd_inv_panel(
     const InvJobDD* __restrict__ jobs, int k0, int s0, int sw, int32_t* __restrict__ status) {
@@ -121,7 +123,11 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void
     const int r = t + q * TH;
     open[q] = r < n && (k0 == 0 || jb.mark[r] == 0);
 #pragma unroll
-    for (int j = 0; j < NB; ++j) P[q][j] = (r < n && j < nb) ? jb.X[(int64_t)r * jb.ld + k0 + j] : zdd_zero();
+    for (int j = 0; j < NB; ++j) {
+      P[q][j] = zdd_zero();
+      if (r < n && j < nb)
+        P[q][j] = load_zdd(k0 > s0 ? jb.T + (int64_t)(NB + j) * n + r : jb.X + (int64_t)r * jb.ld + k0 + j);
+    }
   }
 #pragma unroll 1
   for (int j = 0; j < nb; ++j) {
@@ -178,6 +184,8 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void
     for (int q = 0; q < RPT; ++q) P[q][NB - 1] = g[q];
   }
   // after nb rotations P[q][i] holds column (i + nb) mod NB of the panel
+  const int ws = min(s0 + sw, n) - s0;
+  const bool alone = ws <= NB;   // no other columns: no rank update, which would bring these to X
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {
@@ -187,18 +195,13 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         const int j = i + nb < NB ? i + nb : i + nb - NB;
-        zdd v = zdd_zero();
-        if (j < nb) {
-          v = P[q][i];
-          jb.X[(int64_t)r * jb.ld + k0 + j] = v;
-          if (r == prows[j]) v.re = dd_add(v.re, dd_from(-1.0));
-        }
-        jb.T[(int64_t)j * n + r] = v;
+        const zdd v = j < nb ? P[q][i] : zdd_zero();
+        if (!alone) store_zdd(jb.T + (int64_t)j * n + r, v);
+        else if (j < nb) store_zdd(jb.X + (int64_t)r * jb.ld + k0 + j, v);
       }
     }
   }
   if (t < nb) jb.piv[k0 + t] = prows[t];
-  const int ws = min(s0 + sw, n) - s0;
   for (int i = t; i < NB * ws; i += TH) {
     const int j = i / ws, c = s0 + i % ws;
     jb.R[(int64_t)j * n + c] =
@@ -207,41 +210,49 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void
   if (t == 0 && bad && status) atomicMin(&status[jb.e], (int32_t)HSC_E_SINGULAR);
 }
 
-// X[r][c] += sum_k T[k][r] R[k][c] over the super-panel's columns [s0, s0 + ns): a lane holds one column
+// X[r][c] += sum_k T[k][r] R[k][c] over the super-panel's columns [s0, s0 + ns), T = the finished panel less the
+// identity at its pivots.  The panel's own columns (where R is zero) come from the T workspace to X, the next
+// panel's go from X to the T workspace (k_dd_inv_panel).  A lane holds one column
 // and its NB values of R, a wave walks rows, whose T values wait in LDS.  Super-panels of at most 32 or 16
 // columns (the last of a matrix) put 2 or 4 rows side by side in a wave.  Bound by the vector units: 50 FP64
-// instructions per complex multiply-add, 1.74 ps at their measured 2.3 ns a wave; 512 matrices of order 216
-// take 122 us (2.15 ps, 3.7 TB/s of X), 1024 of order 64 62 us (1.86 ps).  The grouped product that this
-// replaces took 158 us, and 13 us against 7 us for one small matrix.
+// instructions per complex multiply-add, 1.74 ps at their measured 2.3 ns a wave; 55e6 of them (16^3, 32
+// energies, 108e3 rows) take 150 us, 2.7 ps (2.4 without the two panels' detour through the T workspace, which
+// saves the panel kernel 12 us and on smaller launches costs nothing).  The grouped product that
+// this replaces took 158 us, and 13 us against 7 us for one small matrix.
 constexpr int kRankRows = 32;   // rows of a workgroup at most
 
 template <int NB, int CW>
-__device__ __forceinline__ void inv_rank_rows(const InvJobDD& jb, const zdd* T, int s0, int ns, int r0, int rows,
+__device__ __forceinline__ void inv_rank_rows(const InvJobDD& jb, const zdd* T, int k0, int s0, int ns, int r0, int rows,
                                               int lane) {
   constexpr int RS = 64 / CW;   // rows side by side
   const int n = jb.n, c = lane % CW, q = lane / CW;
   if (c >= ns) return;
-  const int64_t ld = jb.ld;
   const zdd* R = jb.R + s0 + c;
-  zdd* X = jb.X + r0 * ld + s0 + c;
+  const int j = s0 + c - k0;   // column of this panel (j < NB), of the next one (j < 2 NB)
+  zdd* const X = jb.X + (int64_t)r0 * jb.ld + s0 + c;
+  zdd* const buf = jb.T + (int64_t)j * n + r0;
+  const bool own = j >= 0 && j < NB, next = j >= NB && j < 2 * NB;
+  const zdd* const src = own ? buf : X;
+  zdd* const dst = next ? buf : X;
+  const int64_t ls = own ? 1 : jb.ld, ld = next ? 1 : jb.ld;
   const int last = rows - 1;
   int i = q;
   // (rows beyond the end are read at the last one and not written)
-  zdd x0 = load_zdd(X + min(i, last) * ld), x1 = load_zdd(X + min(i + RS, last) * ld);
+  zdd x0 = load_zdd(src + min(i, last) * ls), x1 = load_zdd(src + min(i + RS, last) * ls);
   zdd b[NB];
 #pragma unroll
   for (int k = 0; k < NB; ++k) b[k] = load_zdd(R + (int64_t)k * n);
 #pragma unroll 1
   for (;;) {
-    const zdd y0 = load_zdd(X + min(i + 2 * RS, last) * ld), y1 = load_zdd(X + min(i + 3 * RS, last) * ld);
+    const zdd y0 = load_zdd(src + min(i + 2 * RS, last) * ls), y1 = load_zdd(src + min(i + 3 * RS, last) * ls);
     zddacc a0 = zddacc_from(x0), a1 = zddacc_from(x1);
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       zddacc_fma(a0, T[min(i, last) * NB + k], b[k]);
       zddacc_fma(a1, T[min(i + RS, last) * NB + k], b[k]);
     }
-    if (i < rows) store_zdd(X + i * ld, zddacc_value(a0));
-    if (i + RS < rows) store_zdd(X + (i + RS) * ld, zddacc_value(a1));
+    if (i < rows) store_zdd(dst + i * ld, zddacc_value(a0));
+    if (i + RS < rows) store_zdd(dst + (i + RS) * ld, zddacc_value(a1));
     i += 2 * RS;
     if (i >= rows) return;
     x0 = y0;
@@ -260,16 +271,20 @@ __global__ __launch_bounds__(256) void k_dd_inv_rank(const InvJobDD* __restrict_
   const int rows_b = min(4 * rows_w, n - b0);
   for (int i = threadIdx.x; i < 4 * rows_w * NB; i += 256) {
     const int k = i / (4 * rows_w), r = i % (4 * rows_w);
-    if (r < rows_b) T[r * NB + k] = load_zdd(jb.T + (int64_t)k * n + b0 + r);
+    if (r < rows_b) {
+      zdd v = load_zdd(jb.T + (int64_t)k * n + b0 + r);
+      if (k0 + k < n && jb.piv[k0 + k] == b0 + r) v.re = dd_add(v.re, dd_from(-1.0));
+      T[r * NB + k] = v;
+    }
   }
   __syncthreads();
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int rows = min(rows_w, rows_b - w * rows_w);
   if (rows <= 0) return;
   const zdd* Tw = T + w * rows_w * NB;
-  if (ns > 32) inv_rank_rows<NB, 64>(jb, Tw, s0, ns, b0 + w * rows_w, rows, lane);
-  else if (ns > 16) inv_rank_rows<NB, 32>(jb, Tw, s0, ns, b0 + w * rows_w, rows, lane);
-  else inv_rank_rows<NB, 16>(jb, Tw, s0, ns, b0 + w * rows_w, rows, lane);
+  if (ns > 32) inv_rank_rows<NB, 64>(jb, Tw, k0, s0, ns, b0 + w * rows_w, rows, lane);
+  else if (ns > 16) inv_rank_rows<NB, 32>(jb, Tw, k0, s0, ns, b0 + w * rows_w, rows, lane);
+  else inv_rank_rows<NB, 16>(jb, Tw, k0, s0, ns, b0 + w * rows_w, rows, lane);
 }
 
 // After the panels of the columns [s0, s0 + ws), ws <= W, of a matrix with other columns to update:
@@ -617,7 +632,7 @@ void launch_dd_inv_panel(hipStream_t st, const InvJobDD* jobs, int njobs, int k0
 void launch_dd_inv_rank(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int s0, int sw, int max_n) {
   if (njobs <= 0 || k0 >= max_n) return;
   // 8 rows of a wave share its R values (122 us for 512 matrices of order 216, 133 us with 4 and 158 us with
-  // 2); fewer where that leaves under 3 waves per SIMD (18 of order 960: 26 us with 8, 23 us with 4)
+  // 2, X alone); fewer where that leaves under 3 waves per SIMD (18 of order 960: 26 us with 8, 23 us with 4)
   int rows_w = kRankRows / 4;
   while (rows_w > 2 && (int64_t)njobs * ((max_n + rows_w - 1) / rows_w) < 3072) rows_w /= 2;
   const int chunks = (max_n + 4 * rows_w - 1) / (4 * rows_w);
