@@ -39,7 +39,7 @@ def _dot(a, b):
 # columns with 8); super-panels are 64 columns, their remainders up to 16 and 32 columns pack rows in the rank
 # update; beyond 512 a third level of 256 columns.
 @pytest.mark.parametrize("matrix_cores", [0, 1])
-@pytest.mark.parametrize("n", [1, 2, 7, 8, 9, 63, 64, 65, 80, 81, 96, 97, 128, 129, 256, 257, 512, 513, 641, 1024, 1025])
+@pytest.mark.parametrize("n", [1, 2, 7, 8, 9, 63, 64, 65, 80, 81, 96, 97, 128, 129, 256, 257, 512, 513, 641, 1024, 1025, 2049])
 def test_zinv_dd_sizes(ctx, n, matrix_cores):
     # a row permutation of 4 I + G, G with eigenvalues inside the unit circle: condition below 2, pivots off
     # the diagonal.  Each entry of A Y - I sums n products whose factors carry the errors of n elimination
