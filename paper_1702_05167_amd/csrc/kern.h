@@ -249,11 +249,12 @@ void launch_dd_diag(hipStream_t st, const RowJob* jobs, const int32_t* row_job, 
 // frontal assembly in double-double (RowJob.dst and ChildRef.U point to zdd)
 void launch_dd_assemble(hipStream_t st, const RowJob* jobs, const int32_t* row_job, int total_rows,
                         const EnergyScalars* es);
-// the panel of dd_inv_nb(max_n) columns from k0 inside the super-panel [s0, s0 + sw): factored in place,
-// with T and R the factors of the update of the super-panel's other columns
+// the panel of dd_inv_nb(max_n) columns from k0 inside the super-panel [s0, s0 + sw): its finished columns go to
+// the T workspace (to X if the super-panel has no others), the pivot rows of the other columns to R
 void launch_dd_inv_panel(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int s0, int sw, int max_n,
                          int32_t* status);
-// its update of the super-panel's other columns
+// its update of the super-panel's other columns; brings the finished columns to X and leaves the next panel's in
+// the T workspace, where the panel kernel takes them
 void launch_dd_inv_rank(hipStream_t st, const InvJobDD* jobs, int njobs, int k0, int s0, int sw, int max_n);
 void launch_dd_inv_unscramble(hipStream_t st, const InvJobDD* jobs, int njobs, int max_n);
 // T = the columns [s0, s0 + W) minus the identity at their pivots (row stride W), R = their pivot rows;
