@@ -80,25 +80,31 @@ __device__ __forceinline__ zdd zdd_mul(zdd a, zdd b) {
 // acc + a * b
 __device__ __forceinline__ zdd zdd_fma(zdd acc, zdd a, zdd b) { return zdd_add(acc, zdd_mul(a, b)); }
 
-// 1 / d for d in [1, 8]: the FP64 reciprocal and one Newton step with the exact residual
-__device__ __forceinline__ dd dd_rcp(dd d) {
+// 1 / a = conj(a) / |a|^2, scaled by the power of two of the larger component (0 for a = 0).  |a|^2 as d.hi + d.lo + f
+// with the roundings of its low part in f, each component as an FP64 quotient and its residual, so that little but
+// the result's own rounding remains; the FP64 reciprocal y of d.hi is on its way meanwhile.  Error in units of 2^-106 of
+// |1 / a|, mean and worst: 0.44 and 3.2 (0.68 and 5.3 with one Newton step of |a|^-2, 0.48 and 3.5 with three FP64
+// quotients a component); an inverse of order 64 to 512 takes 2 to 4 % longer than with the Newton step.
+__device__ __forceinline__ zdd zdd_rcp(zdd a) {
 #pragma clang fp contract(off)
+  const double s = fmax(fabs(a.re.hi), fabs(a.im.hi));
+  if (s == 0.0) return zdd_zero();
+  const int k = -ilogb(s);
+  const dd x{ldexp(a.re.hi, k), ldexp(a.re.lo, k)}, z{ldexp(a.im.hi, k), ldexp(a.im.lo, k)};
+  const dd p = two_prod(x.hi, x.hi), q = two_prod(z.hi, z.hi), d = two_sum(p.hi, q.hi);   // in [1, 8)
   double y = __builtin_amdgcn_rcp(d.hi);
   y = fma(y, fma(-d.hi, y, 1.0), y);
   y = fma(y, fma(-d.hi, y, 1.0), y);
-  const double r = fma(-d.lo, y, fma(-d.hi, y, 1.0));
-  return quick_two_sum(y, y * r);
-}
-
-// 1 / a = conj(a) / |a|^2, scaled by the power of two of the larger component (0 for a = 0)
-__device__ __forceinline__ zdd zdd_rcp(zdd a) {
-  const double s = fmax(fabs(a.re.hi), fabs(a.im.hi));
-  if (s == 0.0) return zdd_zero();
-  const int e = -ilogb(s);
-  const dd ar{ldexp(a.re.hi, e), ldexp(a.re.lo, e)}, ai{ldexp(a.im.hi, e), ldexp(a.im.lo, e)};
-  const dd q = dd_rcp(dd_add(dd_mul(ar, ar), dd_mul(ai, ai)));   // 1 / |a 2^e|^2, |a 2^e|^2 in [1, 8)
-  const dd re = dd_mul(ar, q), im = dd_mul(dd_neg(ai), q);
-  return zdd{dd{ldexp(re.hi, e), ldexp(re.lo, e)}, dd{ldexp(im.hi, e), ldexp(im.lo, e)}};
+  const dd c = two_sum(p.lo, q.lo), g = two_sum(d.lo, 2.0 * fma(x.hi, x.lo, z.hi * z.lo)), l = two_sum(c.hi, g.hi);
+  const double f = l.lo + (c.lo + g.lo + fma(x.lo, x.lo, z.lo * z.lo)), e = fma(-l.hi, y, fma(-d.hi, y, 1.0));
+  auto over = [&](dd v) {
+    const double h = v.hi * y;
+    const dd r = two_sum(fma(-h, d.hi, v.hi), fma(-h, l.hi, v.lo));
+    const double w = r.hi * y;
+    const dd t = quick_two_sum(h, w + (fma(r.hi, y, -w) + fma(w, e, fma(-h, f, r.lo) * y)));
+    return dd{ldexp(t.hi, k), ldexp(t.lo, k)};
+  };
+  return zdd{over(x), over(dd_neg(z))};
 }
 
 // Pointers loaded from a descriptor are generic to the compiler; as global ones they give global loads and
