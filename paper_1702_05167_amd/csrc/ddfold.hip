@@ -80,23 +80,53 @@ __global__ __launch_bounds__(RB) void k_dd_assemble(const RowJob* __restrict__ j
 // unmarked rows, and the inverse comes out permuted: X[p_j][k] = (A^-1)[j][p_k].
 constexpr int PT = 512;
 
-// largest of 64 lanes, in scalar registers
+// largest of a wave's 64 lanes, or of the last LANES <= 8 of every 16 (which all hold the same keys), in scalar registers
+template <int LANES>
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 #define HSC_DPP_MAX(ctrl) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, false))
-  HSC_DPP_MAX(0x111);   // row_shr 1, 2, 4, 8: lane 15 of every 16 has the row's largest
-  HSC_DPP_MAX(0x112);
-  HSC_DPP_MAX(0x114);
-  HSC_DPP_MAX(0x118);
-  HSC_DPP_MAX(0x142);   // row_bcast 15, 31: lane 63 has the wave's
-  HSC_DPP_MAX(0x143);
+  if (LANES > 1) HSC_DPP_MAX(0x111);   // row_shr 1, 2, 4, 8: lane 15 of every 16 has the row's largest
+  if (LANES > 2) HSC_DPP_MAX(0x112);
+  if (LANES > 4) HSC_DPP_MAX(0x114);
+  if (LANES > 8) HSC_DPP_MAX(0x118);
+  if (LANES > 16) {
+    HSC_DPP_MAX(0x142);   // row_bcast 15, 31: lane 63 has the wave's
+    HSC_DPP_MAX(0x143);
+  }
 #undef HSC_DPP_MAX
-  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, LANES > 16 ? 63 : 15);
+}
+
+// a row that may become the pivot: the bits of its |Re| + |Im| (the upper word plus one, 0 = no row) and its index
+struct alignas(16) PivotKey {
+  uint32_t hi, lo;
+  int row;
+};
+// larger, or as large and the earlier row
+__device__ __forceinline__ bool pivot_before(PivotKey a, PivotKey b) {
+  return a.hi > b.hi || (a.hi == b.hi && (a.lo > b.lo || (a.lo == b.lo && a.row < b.row)));
+}
+// the lane with the first in that order of a wave's keys (of LANES <= 8 keys that the lanes hold in turn): the upper
+// words decide unless two are equal
+template <int LANES>
+__device__ __forceinline__ int pivot_lane(PivotKey k) {
+  constexpr uint64_t lanes = LANES == 64 ? ~0ull : (1ull << (LANES & 63)) - 1;
+  const uint32_t hi = wave_max_u32<LANES>(k.hi);
+  uint64_t at = __ballot(k.hi == hi) & lanes;
+  if (hi != 0 && (at & (at - 1)) != 0) {
+    const uint32_t lo = wave_max_u32<LANES>(k.hi == hi ? k.lo : 0u);
+    const bool equal = k.hi == hi && k.lo == lo;
+    const uint32_t last = wave_max_u32<LANES>(equal ? 4095u - (uint32_t)k.row : 0u);
+    at = __ballot(equal && (uint32_t)k.row == 4095u - last) & lanes;
+  }
+  return __builtin_ctzll(at);
 }
 
 // One panel of NB columns from k0, one workgroup per matrix, each thread RPT rows.  A serial chain of NB
 // column steps: pivot search, reciprocal, update of the panel.  The pivot is the row with the largest
-// leading 8 mantissa bits (and exponent) of |Re| + |Im|, the first of equals: one 32-bit key per row, one
-// maximum.  Every thread forms the reciprocal itself (no round trip through LDS), and the columns
+// |Re| + |Im| in FP64, the first of equals: one maximum over the upper words (20 mantissa bits) finds it unless
+// two of a wave's rows are equal there (inverses of order 128 to 256 take 3 to 5 % longer than with keys of 8
+// mantissa bits and the row in one word; waves offering their rows before the search ends, which saves a barrier,
+// take 4 % more again).  Every thread forms the reciprocal itself (no round trip through LDS), and the columns
 // rotate through the registers so that the step's code is a loop body (the current column is P[.][0]).
 // Columns are read and written a column at a time, rows side by side, in the T workspace: the finished panel
 // as its first NB rows (zero beyond nb), the next panel's columns in the NB rows after (from its rank update; the
@@ -111,7 +141,7 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void
   if (k0 >= n) return;
   const int nb = min(NB, n - k0);
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  __shared__ uint32_t red[2][TH / 64];
+  __shared__ PivotKey red[2][TH / 64];
   __shared__ zdd rowp[2][NB];
   __shared__ int prows[NB];
   bool bad = false;
@@ -132,22 +162,24 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void
 #pragma unroll 1
   for (int j = 0; j < nb; ++j) {
     const int par = j & 1;
-    uint32_t key = 0;
+    // this thread's largest open row, its wave's, the workgroup's
+    PivotKey key{0u, 0u, 0};
 #pragma unroll
     for (int q = 0; q < RPT; ++q)
       if (open[q]) {
-        const uint32_t v = (uint32_t)__double2hiint(zdd_cabs1(P[q][0]));
-        key = max(key, (v & 0xfffff000u) | (uint32_t)(4095 - (t + q * TH)));
+        const double v = zdd_cabs1(P[q][0]);
+        // (a NaN too is a row)
+        const PivotKey c{((uint32_t)__double2hiint(v) & 0x7fffffffu) + 1u, (uint32_t)__double2loint(v), t + q * TH};
+        if (RPT == 1 || pivot_before(c, key)) key = c;
       }
-    key = wave_max_u32(key);
+    int first = pivot_lane<64>(key);
     if (TH > 64) {
-      if (lane == 0) red[par][w] = key;
+      if (lane == first) red[par][w] = key;
       __syncthreads();
-      key = red[par][0];
-#pragma unroll
-      for (int i = 1; i < TH / 64; ++i) key = max(key, red[par][i]);
+      key = red[par][lane % (TH / 64)];
+      first = pivot_lane<(TH > 64 ? TH / 64 : 64)>(key);
     }
-    const int prow = 4095 - (int)(key & 4095u);
+    const int prow = __builtin_amdgcn_readlane(key.row, first);
 #pragma unroll
     for (int q = 0; q < RPT; ++q)
       if (t + q * TH == prow) {
