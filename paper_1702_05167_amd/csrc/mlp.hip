@@ -73,7 +73,7 @@ __global__ __launch_bounds__(NTH) void k_sgemm(int M, int N, int K, const float*
   __shared__ float As[TK][TM + 4];
   __shared__ float Bs[TK][TN + 4];
   const int tid = threadIdx.x;
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
+  const int m0 = blockIdx.x * TM, n0 = blockIdx.y * TN;   // (only x takes the tiles of any number of samples)
   const int tr = tid / 16, tc = tid % 16;
   const int kb = EPI == EPI_GRAD ? (int)blockIdx.z * kc : 0, ke = EPI == EPI_GRAD ? min(K, kb + kc) : K;
   constexpr int NA = TM * TK / NTH, NB = TN * TK / NTH;
@@ -201,7 +201,7 @@ void sgemm(hipStream_t st, int M, int N, int K, const float* A, int64_t am, int6
            int64_t bn, const float* bias, const float* H, float* C, int64_t ldc, int chunks = 1, int kc = 0,
            int64_t cstride = 0) {
   const int cols = EPI == EPI_GRAD ? N + 1 : N;
-  dim3 grid((cols + TN - 1) / TN, (M + TM - 1) / TM, chunks);
+  dim3 grid((unsigned)(((int64_t)M + TM - 1) / TM), (cols + TN - 1) / TN, chunks);
   hipLaunchKernelGGL((k_sgemm<EPI>), grid, dim3(NTH), 0, st, M, N, K, A, am, ak, B, bk, bn, bias, H, C, ldc, kc,
                      cstride);
 }

@@ -1,0 +1,18 @@
+"""The surrogate network at sizes where its tiles, its grid and its workspace change."""
+import numpy as np
+import pytest
+import torch
+
+import oracle.mlp as om
+import paper_1702_05167_amd as pkg
+
+pytestmark = pytest.mark.gpu
+
+
+def test_forward_of_millions_of_samples(ctx):
+    # more than 65,536 tiles of rows, of either height
+    n, widths = 65536 * 64 + 7, (1, 1)
+    net = pkg.MLP(ctx, widths)
+    net.set_params(np.array([3.0, -1.0], np.float32))
+    x = (torch.arange(n, device=ctx.torch_device) % 1021).to(torch.float32)[:, None]
+    assert torch.equal(net.forward(x), 3.0 * x - 1.0)
