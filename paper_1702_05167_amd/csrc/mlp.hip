@@ -36,7 +36,8 @@ struct hsc_mlp {
   float* out = nullptr;                    // network output for the loss, [cap * w_out]
   float* xb = nullptr;                     // gathered batch inputs [cap * w_in]
   float* tb = nullptr;                     // gathered batch targets [cap * w_out]
-  float* part = nullptr;                   // partial gradients, [chunks(cap)][P]
+  float* part = nullptr;                   // partial gradients, [part_chunks][P]
+  int part_chunks = 0;
   float* loss = nullptr;                   // [1] when the caller keeps no loss history
 };
 
@@ -229,15 +230,15 @@ hsc_status reserve(hsc_mlp* m, int64_t n) {
     set_error("device synchronisation failed");
     return HSC_E_HIP;
   }
-  float* old[7] = {m->act, m->dbuf[0], m->dbuf[1], m->out, m->xb, m->tb, m->part};
+  float* old[6] = {m->act, m->dbuf[0], m->dbuf[1], m->out, m->xb, m->tb};
   for (float* p : old)
     if (p) (void)hipFree(p);
-  m->act = m->dbuf[0] = m->dbuf[1] = m->out = m->xb = m->tb = m->part = nullptr;
+  m->act = m->dbuf[0] = m->dbuf[1] = m->out = m->xb = m->tb = nullptr;
   m->cap = 0;
-  const int64_t sizes[7] = {cap * std::max<int64_t>(hidden_sum(m), 1), cap * wmax, cap * wmax,
-                            cap * m->w.back(), cap * m->w.front(), cap * m->w.back(), m->P * grad_chunks(m, cap)};
-  float** dst[7] = {&m->act, &m->dbuf[0], &m->dbuf[1], &m->out, &m->xb, &m->tb, &m->part};
-  for (int i = 0; i < 7; ++i) {
+  const int64_t sizes[6] = {cap * std::max<int64_t>(hidden_sum(m), 1), cap * wmax, cap * wmax,
+                            cap * m->w.back(), cap * m->w.front(), cap * m->w.back()};
+  float** dst[6] = {&m->act, &m->dbuf[0], &m->dbuf[1], &m->out, &m->xb, &m->tb};
+  for (int i = 0; i < 6; ++i) {
     if (hipMalloc(dst[i], sizeof(float) * sizes[i]) != hipSuccess) {
       (void)hipGetLastError();
       set_error("MLP workspace allocation failed");
@@ -245,6 +246,28 @@ hsc_status reserve(hsc_mlp* m, int64_t n) {
     }
   }
   m->cap = cap;
+  return HSC_OK;
+}
+
+// the gradients' chunks for the samples reserved (a network that only evaluates has none)
+hsc_status reserve_part(hsc_mlp* m) {
+  const int chunks = grad_chunks(m, m->cap);
+  if (chunks <= m->part_chunks) return HSC_OK;
+  if (m->part && hipDeviceSynchronize() != hipSuccess) {
+    (void)hipGetLastError();
+    set_error("device synchronisation failed");
+    return HSC_E_HIP;
+  }
+  if (m->part) (void)hipFree(m->part);
+  m->part = nullptr;
+  m->part_chunks = 0;
+  if (hipMalloc(&m->part, sizeof(float) * m->P * chunks) != hipSuccess) {
+    (void)hipGetLastError();
+    m->part = nullptr;
+    set_error("MLP workspace allocation failed");
+    return HSC_E_OOM;
+  }
+  m->part_chunks = chunks;
   return HSC_OK;
 }
 
@@ -387,6 +410,7 @@ hsc_status hsc_mlp_grads(hsc_ctx* ctx, hsc_mlp* m, int64_t n, const float* x, co
   if (!ctx || !m || n <= 0 || n > INT32_MAX || !x || !t || !grads || !loss) { set_error("bad arguments to hsc_mlp_grads"); return HSC_E_ARG; }
   MLPCHK(hipSetDevice(m->device));
   hsc_status rc = reserve(m, n);
+  if (rc == HSC_OK) rc = reserve_part(m);
   if (rc != HSC_OK) return rc;
   loss_and_grads(reinterpret_cast<hipStream_t>(ctx_stream(ctx)), m, n, x, t, grads, loss);
   MLPCHK(hipGetLastError());
@@ -405,6 +429,7 @@ hsc_status hsc_mlp_train(hsc_ctx* ctx, hsc_mlp* m, int64_t n, const float* x, co
   hipStream_t st = reinterpret_cast<hipStream_t>(ctx_stream(ctx));
   const int64_t B = order ? o->batch : n;
   hsc_status rc = reserve(m, B);
+  if (rc == HSC_OK) rc = reserve_part(m);
   if (rc != HSC_OK) return rc;
   const int wi = m->w.front(), wo = m->w.back();
   for (int s = 0; s < o->steps; ++s) {
