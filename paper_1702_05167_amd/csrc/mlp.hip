@@ -53,20 +53,24 @@ namespace {
     }                                                                               \
   } while (0)
 
-// 32 x 64 tiles: 256 workgroups for a 2048 x 256 layer
-constexpr int TM = 32, TN = 64, TK = 32, NTH = 256;
+// Tiles of TM x 64, TK deep: 32 x 64 x 32 (256 workgroups for a 2048 x 256 layer), 64 x 64 x 16 where those give every
+// CU four workgroups (half the LDS reads per operation, half the LDS; without either limit a forward pass of
+// 524288 samples, 256 wide, takes 3.08 ms in 32 x 64 x 32, 2.38 in 64 x 64 x 32 and 1.58 in 64 x 64 x 16, 2.74 in the
+// latter without loads ahead; 4096 samples, 256 tiles of 64 rows: 0.080 and 0.109)
+constexpr int TN = 64, NTH = 256;
+constexpr int64_t kWideTiles = 1024;
 constexpr int kMaxChunks = 64;           // sample chunks of the gradients
 constexpr int64_t kPartFloats = 1 << 24;   // and the most partial gradients they may fill
 
 enum Epi { EPI_BIAS_TANH = 1, EPI_BIAS = 2, EPI_TANH_BACK = 3, EPI_GRAD = 4 };
 
 // C[m][n] (row stride ldc) = sum_k A(m, k) B(k, n), A(m, k) = A[m*am + k*ak], B(k, n) = B[k*bk + n*bn]
-// (am or ak and bk or bn are 1: lanes run along that index)
+// (am or ak and bk or bn are 1: lanes run along that index, except along a short k)
 // EPI_BIAS_TANH: tanh(acc + bias[n]); EPI_BIAS: acc + bias[n];
 // EPI_TANH_BACK: acc * (1 - H[m][n]^2) with H the tanh output the gradient flows back through.
 // EPI_GRAD: the chunk blockIdx.z of kc values of k, B with a column of ones at n = N whose products
 // (the bias gradient) follow the M x N block; chunk c goes to C + c * cstride.
-template <int EPI>
+template <int EPI, int TM, int TK>
 __global__ __launch_bounds__(NTH) void k_sgemm(int M, int N, int K, const float* __restrict__ A, int64_t am,
                                                int64_t ak, const float* __restrict__ B, int64_t bk, int64_t bn,
                                                const float* __restrict__ bias, const float* __restrict__ H,
@@ -78,45 +82,50 @@ __global__ __launch_bounds__(NTH) void k_sgemm(int M, int N, int K, const float*
   const int tr = tid / 16, tc = tid % 16;
   const int kb = EPI == EPI_GRAD ? (int)blockIdx.z * kc : 0, ke = EPI == EPI_GRAD ? min(K, kb + kc) : K;
   constexpr int NA = TM * TK / NTH, NB = TN * TK / NTH;
+  const bool a_along_k = ak == 1 && K >= TK / 2, b_along_k = bk == 1 && K >= TK / 2;
   float ra[NA], rb[NB];
   auto fetch = [&](int k0) {
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       const int e = tid + i * NTH;
-      const int m = m0 + (ak == 1 ? e / TK : e % TM), k = k0 + (ak == 1 ? e % TK : e / TM);
+      const int m = m0 + (a_along_k ? e / TK : e % TM), k = k0 + (a_along_k ? e % TK : e / TM);
       ra[i] = (m < M && k < ke) ? A[m * am + k * ak] : 0.f;
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int e = tid + i * NTH;
-      const int n = n0 + (bk == 1 ? e / TK : e % TN), k = k0 + (bk == 1 ? e % TK : e / TN);
+      const int n = n0 + (b_along_k ? e / TK : e % TN), k = k0 + (b_along_k ? e % TK : e / TN);
       rb[i] = k >= ke ? 0.f : n < N ? B[k * bk + n * bn] : (EPI == EPI_GRAD && n == N) ? 1.f : 0.f;
     }
   };
-  float acc[2][4] = {};
+  constexpr int RM = TM / 16;   // rows of a thread
+  float acc[RM][4] = {};
   fetch(kb);
   for (int k0 = kb; k0 < ke; k0 += TK) {
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       const int e = tid + i * NTH;
-      As[ak == 1 ? e % TK : e / TM][ak == 1 ? e / TK : e % TM] = ra[i];
+      As[a_along_k ? e % TK : e / TM][a_along_k ? e / TK : e % TM] = ra[i];
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int e = tid + i * NTH;
-      Bs[bk == 1 ? e % TK : e / TN][bk == 1 ? e / TK : e % TN] = rb[i];
+      Bs[b_along_k ? e % TK : e / TN][b_along_k ? e / TK : e % TN] = rb[i];
     }
     __syncthreads();
     if (k0 + TK < ke) fetch(k0 + TK);
-#pragma unroll 8
-    for (int kk = 0; kk < TK; ++kk) {
-      float a[2], b[4];
+    const int depth = (min(TK, ke - k0) + 7) & ~7;   // (zeros beyond ke)
+#pragma unroll 1
+    for (int k8 = 0; k8 < depth; k8 += 8)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = As[kk][tr * 2 + i];
+    for (int kk = k8; kk < k8 + 8; ++kk) {
+      float a[RM], b[4];
+#pragma unroll
+      for (int i = 0; i < RM; ++i) a[i] = As[kk][tr * RM + i];
 #pragma unroll
       for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tc * 4 + j];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < RM; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
     }
@@ -124,8 +133,8 @@ __global__ __launch_bounds__(NTH) void k_sgemm(int M, int N, int K, const float*
   }
   if (EPI == EPI_GRAD) C += blockIdx.z * cstride;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int m = m0 + tr * 2 + i;
+  for (int i = 0; i < RM; ++i) {
+    const int m = m0 + tr * RM + i;
     if (m >= M) continue;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -201,10 +210,13 @@ template <int EPI>
 void sgemm(hipStream_t st, int M, int N, int K, const float* A, int64_t am, int64_t ak, const float* B, int64_t bk,
            int64_t bn, const float* bias, const float* H, float* C, int64_t ldc, int chunks = 1, int kc = 0,
            int64_t cstride = 0) {
-  const int cols = EPI == EPI_GRAD ? N + 1 : N;
-  dim3 grid((unsigned)(((int64_t)M + TM - 1) / TM), (cols + TN - 1) / TN, chunks);
-  hipLaunchKernelGGL((k_sgemm<EPI>), grid, dim3(NTH), 0, st, M, N, K, A, am, ak, B, bk, bn, bias, H, C, ldc, kc,
-                     cstride);
+  const int64_t cols = EPI == EPI_GRAD ? N + 1 : N, tn = (cols + TN - 1) / TN;
+  auto run = [&](auto kernel, int tm) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(((int64_t)M + tm - 1) / tm), (unsigned)tn, chunks), dim3(NTH), 0, st, M, N,
+                       K, A, am, ak, B, bk, bn, bias, H, C, ldc, kc, cstride);
+  };
+  if (EPI != EPI_GRAD && ((int64_t)M + 63) / 64 * tn >= kWideTiles) run(k_sgemm<EPI == EPI_GRAD ? EPI_BIAS : EPI, 64, 16>, 64);
+  else run(k_sgemm<EPI, 32, 32>, 32);
 }
 
 // sample chunks of the gradients of n samples: 64 samples each, more once kMaxChunks or the partial
