@@ -153,7 +153,10 @@ typedef struct {
    *     about K 2^-109 times the product of the largest row and column entries,
    *     rounded to double-double; products with K < 32, the rank-8 updates of
    *     the pivot-block inverses among them, stay on the vector units).
-   *     Needs a residue scratch of up to 4 GiB besides the workspace.
+   *     Needs a residue scratch of up to 4 GiB besides the workspace, which
+   *     also holds the residues (64 B per complex element) of operands that
+   *     several products share; where it does not fit, those are formed for
+   *     each product (same results, less memory, slower).
    * The unpivoted cluster elimination amplifies rounding errors by up to
    * ~1/sigma_min(A_ii)^2 at energies where a cluster block A_ii is nearly
    * singular (outside the lead band, where nothing broadens it): in the fold

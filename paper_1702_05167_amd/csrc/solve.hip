@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -201,6 +202,7 @@ struct Builder {
   bool ddx = false;   // double-double extraction as well (G, the lesser channels)
   bool oz = false;    // double-double products from int8 residues on the integer matrix cores
   int slices = kOzSlices;   // digits per operand of those products
+  bool keep = true;   // residues of operands used by several products stay in the workspace
   size_t oz_need = 0; // largest residue scratch of one such product step
   size_t ws = 0;  // workspace bytes
   Blob blob;
@@ -223,7 +225,7 @@ struct Builder {
     size_t NF[kMaxChannels], NFc[kMaxChannels], M[kMaxChannels], PX[kMaxChannels], PFF[kMaxChannels],
         PT[kMaxChannels];
     // residues of operands used by several products (precision 3): Psi (rows n, depth f),
-    // Psi^T and A_ii^-1 of separators (rows f / n, depth n); 0 = none
+    // Psi^T and A_ii^-1 of separators (rows f / n, depth n); 0 = none, kOzResplit = split for each product
     size_t PsiS, PsiTS, InvS;
   };
   std::vector<CS> cs;   // [cluster * B + slot]
@@ -301,10 +303,10 @@ struct Builder {
         if (ddf) {
           s.Invd = wsa(n * n * 32);
           if (!root(i)) s.Psid = wsa(n * f * 32);
-          if (oz && !root(i) && (int)f >= kOzMinK) s.PsiS = wsa(oz_bytes((int)n, (int)f));
+          if (oz && !root(i) && (int)f >= kOzMinK) s.PsiS = keep ? wsa(oz_bytes((int)n, (int)f)) : kOzResplit;
           if (oz && !root(i) && !leaf(i) && (int)n >= kOzMinK) {
-            s.PsiTS = wsa(oz_bytes((int)f, (int)n));
-            s.InvS = wsa(oz_bytes((int)n, (int)n));
+            s.PsiTS = keep ? wsa(oz_bytes((int)f, (int)n)) : kOzResplit;
+            s.InvS = keep ? wsa(oz_bytes((int)n, (int)n)) : kOzResplit;
           }
         }
         if (!root(i)) s.Psi = wsa(n * f * 16);
@@ -620,7 +622,7 @@ struct Builder {
 
   struct GPD {
     const zdd *A, *B, *C; zdd* D; double2* D64; int M, N, K, lda, ldb, ldc, ldd, ldd64;
-    size_t sa = 0;   // workspace offset of op(A)'s kept residues (0: split into the step's scratch)
+    size_t sa = 0;   // workspace offset of op(A)'s kept residues (0, kOzResplit: split into the step's scratch)
     // Gauss-Jordan update (matrix cores): A minus the identity at the rows piv[k], B's row k is piv[k]
     const int32_t* piv = nullptr;
   };
@@ -630,6 +632,9 @@ struct Builder {
   // runs on the integer matrix cores; the others, and every product without `oz`, on the FP64
   // vector units.
   static constexpr int kOzMinK = 32;
+  // in the place of a kept buffer's offset (those are multiples of 256): the operand has none in this plan, and its
+  // products are routed as if it had, so that results do not depend on the memory that was free
+  static constexpr size_t kOzResplit = 1;
   static constexpr size_t kOzStepCap = size_t(4) << 30;   // residue scratch of one product step
   // Measured costs on the target (seconds): splitting one complex double-double element into
   // residues, one padded multiply-add and one output of the residue product, one multiply-add on the
@@ -705,13 +710,14 @@ struct Builder {
       for (; i < ps.size(); ++i) {
         const GPD& g = ps[i];
         if (g.M <= 0 || g.N <= 0) continue;
-        const size_t need = (g.sa ? 0 : oz_bytes(g.M, g.K)) + oz_bytes(g.N, g.K);
+        const size_t kept = g.sa == kOzResplit ? 0 : g.sa;
+        const size_t need = (kept ? 0 : oz_bytes(g.M, g.K)) + oz_bytes(g.N, g.K);
         if (i > i0 && cur + need > kOzStepCap) break;
-        const auto a = opA == 0 ? operand(g.A, g.lda, 1, g.M, g.K, g.sa, g.piv, kOzMinusPivots)
-                                : operand(g.A, 1, g.lda, g.M, g.K, g.sa, nullptr, kOzPlain);
+        const auto a = opA == 0 ? operand(g.A, g.lda, 1, g.M, g.K, kept, g.piv, kOzMinusPivots)
+                                : operand(g.A, 1, g.lda, g.M, g.K, kept, nullptr, kOzPlain);
         const auto b = opB == 0 ? operand(g.B, 1, g.ldb, g.N, g.K, 0, g.piv, kOzPivotRows)
                                 : operand(g.B, g.ldb, 1, g.N, g.K, 0, nullptr, kOzPlain);
-        kept_a.push_back(g.sa ? 1 : 0);
+        kept_a.push_back(kept ? 1 : 0);
         GemmProbOZ p{};
         p.A8 = reinterpret_cast<const int8_t*>(a.first);
         p.ea = reinterpret_cast<const int32_t*>(a.second);
@@ -1783,48 +1789,9 @@ hsc_status upload_plan(Builder& b, Plan* pl) {
 }
 
 // slices: 7-bit digits per operand of the integer-matrix-core products (precision 3), kOzSlices
-// for the other precisions
-// Plan of this shape and instance (a call with concurrent batches holds instances 0 .. inst - 1 of
-// the shape while it builds instance inst: nothing here frees those).
-int build_plan(hsc_ctx* ctx, const hsc_tree* t, int B, uint32_t want, int prec, int tune, int m3, int slices,
-               Plan** out, int inst = 0) {
-  auto same_shape = [&](const Plan& p) {
-    return p.uid == t->uid && p.B == B && p.want == want && p.prec == prec && p.tune == tune && p.m3 == m3 &&
-           p.slices == slices;
-  };
-  auto held = [&](const std::unique_ptr<Plan>& p) { return same_shape(*p) && p->inst < inst; };
-  for (size_t k = 0; k < ctx->plans.size(); ++k)
-    if (same_shape(*ctx->plans[k]) && ctx->plans[k]->inst == inst) {
-      // most recently used goes last
-      std::unique_ptr<Plan> p = std::move(ctx->plans[k]);
-      ctx->plans.erase(ctx->plans.begin() + k);
-      ctx->plans.push_back(std::move(p));
-      *out = ctx->plans.back().get();
-      return HSC_OK;
-    }
-  // keep memory bounded: drop plans of this tree with other shapes, then the
-  // least recently used ones beyond a few
-  ctx->plans.erase(std::remove_if(ctx->plans.begin(), ctx->plans.end(),
-                                  [&](const std::unique_ptr<Plan>& p) { return p->uid == t->uid && !same_shape(*p); }),
-                   ctx->plans.end());
-  HIPCHK(hipSetDevice(ctx->device));
-  if (ctx->stream) { HIPCHK(hipStreamSynchronize(ctx->stream)); }
-  else { HIPCHK(hipDeviceSynchronize()); }
-  for (size_t k = 0; ctx->plans.size() > (size_t)std::max(3, inst + 1) && k < ctx->plans.size();)
-    if (held(ctx->plans[k])) ++k;
-    else ctx->plans.erase(ctx->plans.begin() + k);
-  // drop every plan but the ones this call holds (to make room)
-  auto drop_unheld = [&]() {
-    ctx->plans.erase(std::remove_if(ctx->plans.begin(), ctx->plans.end(),
-                                    [&](const std::unique_ptr<Plan>& p) { return !held(p); }),
-                     ctx->plans.end());
-  };
-  for (const Cluster& c : t->cl)
-    if (c.n > kMaxCluster) {
-      set_error("cluster of " + std::to_string(c.n) + " sites exceeds the dense-block limit of " +
-                std::to_string(kMaxCluster) + " (use a smaller leaf side)");
-      return HSC_E_ARG;
-    }
+// for the other precisions; keep: see Builder::keep; drop_unheld() makes room
+int make_plan(hsc_ctx* ctx, const hsc_tree* t, int B, uint32_t want, int prec, int tune, int m3, int slices, int inst,
+              bool keep, const std::function<void()>& drop_unheld, Plan** out) {
   std::unique_ptr<Plan> pl(new Plan());
   pl->uid = t->uid; pl->B = B; pl->want = want; pl->n = t->n; pl->prec = prec; pl->tune = tune; pl->m3 = m3;
   pl->slices = slices; pl->inst = inst;
@@ -1833,6 +1800,7 @@ int build_plan(hsc_ctx* ctx, const hsc_tree* t, int B, uint32_t want, int prec, 
   b.ddx = prec >= 2;
   b.oz = prec == 3;
   b.slices = slices;
+  b.keep = keep;
   b.channels();
   b.layout();
   b.layout_faces();
@@ -1904,6 +1872,53 @@ int build_plan(hsc_ctx* ctx, const hsc_tree* t, int B, uint32_t want, int prec, 
   *out = pl.get();
   ctx->plans.push_back(std::move(pl));
   return HSC_OK;
+}
+
+// Plan of this shape and instance (a call with concurrent batches holds instances 0 .. inst - 1 of
+// the shape while it builds instance inst: nothing here frees those).
+int build_plan(hsc_ctx* ctx, const hsc_tree* t, int B, uint32_t want, int prec, int tune, int m3, int slices,
+               Plan** out, int inst = 0) {
+  auto same_shape = [&](const Plan& p) {
+    return p.uid == t->uid && p.B == B && p.want == want && p.prec == prec && p.tune == tune && p.m3 == m3 &&
+           p.slices == slices;
+  };
+  auto held = [&](const std::unique_ptr<Plan>& p) { return same_shape(*p) && p->inst < inst; };
+  for (size_t k = 0; k < ctx->plans.size(); ++k)
+    if (same_shape(*ctx->plans[k]) && ctx->plans[k]->inst == inst) {
+      // most recently used goes last
+      std::unique_ptr<Plan> p = std::move(ctx->plans[k]);
+      ctx->plans.erase(ctx->plans.begin() + k);
+      ctx->plans.push_back(std::move(p));
+      *out = ctx->plans.back().get();
+      return HSC_OK;
+    }
+  // keep memory bounded: drop plans of this tree with other shapes, then the
+  // least recently used ones beyond a few
+  ctx->plans.erase(std::remove_if(ctx->plans.begin(), ctx->plans.end(),
+                                  [&](const std::unique_ptr<Plan>& p) { return p->uid == t->uid && !same_shape(*p); }),
+                   ctx->plans.end());
+  HIPCHK(hipSetDevice(ctx->device));
+  if (ctx->stream) { HIPCHK(hipStreamSynchronize(ctx->stream)); }
+  else { HIPCHK(hipDeviceSynchronize()); }
+  for (size_t k = 0; ctx->plans.size() > (size_t)std::max(3, inst + 1) && k < ctx->plans.size();)
+    if (held(ctx->plans[k])) ++k;
+    else ctx->plans.erase(ctx->plans.begin() + k);
+  // drop every plan but the ones this call holds (to make room)
+  auto drop_unheld = [&]() {
+    ctx->plans.erase(std::remove_if(ctx->plans.begin(), ctx->plans.end(),
+                                    [&](const std::unique_ptr<Plan>& p) { return !held(p); }),
+                     ctx->plans.end());
+  };
+  for (const Cluster& c : t->cl)
+    if (c.n > kMaxCluster) {
+      set_error("cluster of " + std::to_string(c.n) + " sites exceeds the dense-block limit of " +
+                std::to_string(kMaxCluster) + " (use a smaller leaf side)");
+      return HSC_E_ARG;
+    }
+  // where a plan with kept residues does not fit, one that splits those operands for each product
+  const int rc = make_plan(ctx, t, B, want, prec, tune, m3, slices, inst, true, drop_unheld, out);
+  return rc == HSC_E_OOM && prec == 3 ? make_plan(ctx, t, B, want, prec, tune, m3, slices, inst, false, drop_unheld, out)
+                                      : rc;
 }
 
 size_t plan_bytes_per_slot(const hsc_tree* t, uint32_t want, int prec, int slices) {
