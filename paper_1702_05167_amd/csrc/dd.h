@@ -83,7 +83,7 @@ __device__ __forceinline__ zdd zdd_fma(zdd acc, zdd a, zdd b) { return zdd_add(a
 // 1 / a = conj(a) / |a|^2, scaled by the power of two of the larger component (0 for a = 0).  |a|^2 as d.hi + d.lo + f
 // with the roundings of its low part in f, each component as an FP64 quotient and its residual, so that little but
 // the result's own rounding remains; the FP64 reciprocal y of d.hi is on its way meanwhile.  Error in units of 2^-106 of
-// |1 / a|, mean and worst: 0.44 and 3.2 (0.68 and 5.3 with one Newton step of |a|^-2, 0.48 and 3.5 with three FP64
+// |1 / a|, mean and worst: 0.43 and 3.4 (0.68 and 5.3 with one Newton step of |a|^-2, 0.48 and 3.5 with three FP64
 // quotients a component); an inverse of order 64 to 512 takes 2 to 4 % longer than with the Newton step.
 __device__ __forceinline__ zdd zdd_rcp(zdd a) {
 #pragma clang fp contract(off)
@@ -95,7 +95,7 @@ __device__ __forceinline__ zdd zdd_rcp(zdd a) {
   double y = __builtin_amdgcn_rcp(d.hi);
   y = fma(y, fma(-d.hi, y, 1.0), y);
   y = fma(y, fma(-d.hi, y, 1.0), y);
-  const dd c = two_sum(p.lo, q.lo), g = two_sum(d.lo, 2.0 * fma(x.hi, x.lo, z.hi * z.lo)), l = two_sum(c.hi, g.hi);
+  const dd c = two_sum(p.lo, fma(2.0 * x.hi, x.lo, q.lo)), g = two_sum(d.lo, 2.0 * z.hi * z.lo), l = two_sum(c.hi, g.hi);
   const double f = l.lo + (c.lo + g.lo + fma(x.lo, x.lo, z.lo * z.lo)), e = fma(-l.hi, y, fma(-d.hi, y, 1.0));
   auto over = [&](dd v) {
     const double h = v.hi * y;
