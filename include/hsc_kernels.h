@@ -58,6 +58,9 @@ hsc_status hsc_kern_zgemm_tile(hsc_ctx* ctx, int32_t tile_kind, int32_t opA, int
  * (the products of hsc_solve_opts.slices = 15): K 2^-102 instead of K 2^-109,
  * K <= 11648.  beta is 0 or 1; C
  * may equal D and may be NULL when beta = 0.  Synchronous.
+ * Configs 3 and 4 keep their scratch with the context up to 96 MiB (64 B per
+ * element of both operands, M and N rounded up to 32 and K to 64); a larger one
+ * is allocated for the call.
  * Errors: HSC_E_ARG (sizes < 0, bad op or config, leading dimension too small,
  * K beyond the limit of config 3 or 4), HSC_E_OOM, HSC_E_HIP. */
 hsc_status hsc_kern_zgemm_dd(hsc_ctx* ctx, int32_t config, int32_t opA, int32_t opB, int32_t M, int32_t N,
