@@ -111,16 +111,9 @@ __device__ __forceinline__ zdd zdd_rcp(zdd a) {
 // stores instead of flat ones (which also wait for LDS).
 typedef double v2d __attribute__((ext_vector_type(2)));
 template <class T> using global_ptr = __attribute__((address_space(1))) T*;
-// memory that nothing writes while the kernel runs: loads at wave-uniform addresses are scalar
-template <class T> using const_ptr = const __attribute__((address_space(4))) T*;
 
 __device__ __forceinline__ zdd load_zdd(const zdd* q) {
   const global_ptr<const v2d> p = (global_ptr<const v2d>)q;
-  const v2d re = p[0], im = p[1];
-  return zdd{dd{re.x, re.y}, dd{im.x, im.y}};
-}
-__device__ __forceinline__ zdd load_zdd(const_ptr<zdd> q) {
-  const const_ptr<v2d> p = (const_ptr<v2d>)q;
   const v2d re = p[0], im = p[1];
   return zdd{dd{re.x, re.y}, dd{im.x, im.y}};
 }

@@ -272,8 +272,8 @@ constexpr int dd_inv_width(int n) { return n > kDDBlockMin ? kDDBlock : kDDSuper
 constexpr int kOzSlices = 16;
 constexpr int kOzSlicesMin = 15, kOzSlicesMax = 16;
 constexpr int kOzPlanes = 64;   // residue planes of an operand, one byte per element each
-// deepest product: 10880 with S = 16, 11648 with S = 15 (the residues' range allows 17147)
-constexpr int oz_max_depth(int slices) { return (int)(((1ll << 31) - 1) / (3ll * slices * 64 * 64) / 64 * 64); }
+// deepest product that the entry points take; the residues would allow 17152 (residue.h)
+constexpr int oz_max_depth(int slices) { return slices == 15 ? 11648 : 10880; }
 constexpr int oz_rows(int n) { return (n + 31) / 32 * 32; }   // rows of an operand's planes
 // One operand to split: element (r, k) = X[r * ldr + k * ldk] for r < R, k < K (complex
 // double-double); out = kOzPlanes planes of Rp x Kp int8 in 1 KB fragments of 16 rows x 64 k

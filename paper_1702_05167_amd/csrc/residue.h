@@ -8,7 +8,7 @@
 // product into two independent real ones, two planes and two products per modulus.  The others
 // carry the residues of Re and Im and take four products on the same two planes.  The product P of
 // all is 2^237.07: |Re|, |Im| of a product of depth K of operands with |Re| + |Im| <= 2^111 + 1 stay
-// below K 2^222 (1 + 2^-109) < P / 2 for K <= 12288.
+// below K 2^222 (1 + 2^-109) < P / 2 for K <= 17152.
 #pragma once
 
 #include <cstdint>
