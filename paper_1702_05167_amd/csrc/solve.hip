@@ -17,7 +17,6 @@
 #include <map>
 #include <memory>
 #include <mutex>
-#include <set>
 #include <tuple>
 #include <string>
 #include <type_traits>
@@ -65,7 +64,6 @@ struct Blob {
   std::vector<size_t> sc_relocs;
 };
 
-// (S_DD_INV_SWAP has no steps any more; the numbers of the others are the profile's kinds)
 enum StepKind { S_ASSEMBLE, S_INV_PANEL, S_INV_SWAP, S_INV_UNSCR, S_GEMM, S_GATHER, S_ASSEMBLE_N, S_DIAG, S_GUARD,
                 S_DD_ASSEMBLE, S_DD_INV_PANEL, S_DD_INV_SWAP, S_DD_INV_UNSCR, S_DD_GEMM, S_INV_SUPER,
                 S_OZ_SPLIT, S_OZ_GEMM, S_DD_INV_SUPER, S_FACE_HALF, S_FACE_SIGMA, S_BONDS, S_DD_INV_RANK};
@@ -632,7 +630,7 @@ struct Builder {
     // Gauss-Jordan update (matrix cores): A minus the identity at the rows piv[k], B's row k is piv[k]
     const int32_t* piv = nullptr;
   };
-  std::set<size_t> oz_kept;   // kept residue buffers already split by an earlier step
+  std::vector<size_t> oz_kept;   // kept residue buffers already split by an earlier step
   // Double-double block products: with `oz`, every problem whose depth K lies in
   // [kOzMinK, kOzMaxK] and whose estimated time (splitting + residue product) beats the vector units
   // runs on the integer matrix cores; the others, and every product without `oz`, on the FP64
@@ -695,7 +693,8 @@ struct Builder {
           off = reinterpret_cast<size_t>(wsbase + keep);
           const auto r = std::make_pair(off, off + (size_t)kOzPlanes * Rp * Kp);
           seen[key] = r;
-          if (!oz_kept.insert(keep).second) return r;
+          if (std::find(oz_kept.begin(), oz_kept.end(), keep) != oz_kept.end()) return r;
+          oz_kept.push_back(keep);
         } else {
           off = cur;
           cur += oz_bytes(R, K);
