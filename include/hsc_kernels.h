@@ -89,10 +89,11 @@ hsc_status hsc_kern_zgemm_dd_noalloc(hsc_ctx* ctx, int32_t opA, int32_t opB, int
 
 /* The pivot-block inverse of the double-double fold (hsc_solve_opts.precision
  * >= 1, Algorithm 1's A_ii^-1) on its own, with the solver's own launch
- * sequence: two-level blocked Gauss-Jordan with partial pivoting inside the
- * block, in complex double-double (panels of 8, 4 or 2 columns inside
- * super-panels of 64; each super-panel's pivot rows update the other columns in
- * one rank-64 product, on the integer matrix cores when matrix_cores = 1 as with
+ * sequence: blocked Gauss-Jordan with partial pivoting inside the block, in
+ * complex double-double (panels of 8, 4 or 2 columns inside super-panels of 64;
+ * each super-panel's pivot rows update the other columns in one rank-64 product,
+ * beyond n = 512 those of its block of 256 columns, which updates the rest in one
+ * rank-256 product, on the integer matrix cores when matrix_cores = 1 as with
  * precision 3, else on the vector units).  X (order n, leading dimension ld,
  * 32-byte elements as in hsc_kern_zgemm_dd; device) is overwritten; Y (ldy)
  * receives X^-1.  status (device int32, may be NULL) receives 0 or

@@ -64,6 +64,7 @@ struct Blob {
   std::vector<size_t> sc_relocs;
 };
 
+// (S_DD_INV_SWAP has no steps any more; the numbers of the others are the profile's kinds)
 enum StepKind { S_ASSEMBLE, S_INV_PANEL, S_INV_SWAP, S_INV_UNSCR, S_GEMM, S_GATHER, S_ASSEMBLE_N, S_DIAG, S_GUARD,
                 S_DD_ASSEMBLE, S_DD_INV_PANEL, S_DD_INV_SWAP, S_DD_INV_UNSCR, S_DD_GEMM, S_INV_SUPER,
                 S_OZ_SPLIT, S_OZ_GEMM, S_DD_INV_SUPER, S_FACE_HALF, S_FACE_SIGMA, S_BONDS, S_DD_INV_RANK};
