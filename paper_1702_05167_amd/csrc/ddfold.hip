@@ -131,8 +131,8 @@ __device__ __forceinline__ int pivot_lane(PivotKey k) {
 // Columns are read and written a column at a time, rows side by side, in the T workspace: the finished panel
 // as its first NB rows (zero beyond nb), the next panel's columns in the NB rows after (from its rank update; the
 // first panel of a super-panel comes from X).  Row by row in X every lane touched a line of its own: 39 and 62 us
-// a panel for n = 500 and 1024 (4 matrices) instead of 30 and 48.  Also written: R (NB x n) = the pivot rows' old values
-// in the other columns of the super-panel (zero in the panel's own and beyond its nb columns).
+// a panel for n = 500 and 1024 (4 matrices) instead of 30 and 48 (with the keys of 8 bits).  Also written: R (NB x n) =
+// the pivot rows' old values in the other columns of the super-panel (zero in the panel's own and beyond its nb columns).
 template <int TH, int RPT, int NB>
 __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_dd_inv_panel(
     const InvJobDD* __restrict__ jobs, int k0, int s0, int sw, int32_t* __restrict__ status) {
