@@ -56,7 +56,7 @@ namespace {
 // Tiles of TM x 64, TK deep: 32 x 64 x 32 (256 workgroups for a 2048 x 256 layer), 64 x 64 x 16 where those give every
 // CU four workgroups (half the LDS reads per operation, half the LDS; without either limit a forward pass of
 // 524288 samples, 256 wide, takes 3.08 ms in 32 x 64 x 32, 2.38 in 64 x 64 x 32 and 1.58 in 64 x 64 x 16, 2.74 in the
-// latter without loads ahead; 4096 samples, 256 tiles of 64 rows: 0.080 and 0.109)
+// latter without loads ahead; 4096 samples, 256 tiles of 64 rows: 0.080 in the first, 0.109 in the last)
 constexpr int TN = 64, NTH = 256;
 constexpr int64_t kWideTiles = 1024;
 constexpr int kMaxChunks = 64;           // sample chunks of the gradients

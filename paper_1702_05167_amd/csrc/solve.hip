@@ -2717,8 +2717,8 @@ namespace {
 size_t oz_pad(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // one product on the integer matrix cores (split A', split B', residue product), synchronous.  The context keeps
-// the scratch of products up to kKernScratch: allocating and freeing it costs 12 us, 40 us beyond 2 MiB (256 x 256 x 64:
-// 48 of 89 us) and 0.3 to 2.8 ms beyond 64 MiB (33 x 2000 x 500, 0.13 ms by itself)
+// the scratch of products up to kKernScratch: allocating it for each call costs little below 2 MiB, 30 us beyond
+// (256 x 256 x 64: 89 us, 58 with it kept) and 0.3 to 2.8 ms beyond 64 MiB (33 x 2000 x 500: 135 us with it kept)
 constexpr size_t kKernScratch = size_t(96) << 20;
 hsc_status kern_zgemm_oz(hsc_ctx* ctx, int slices, int opA, int opB, int M, int N, int K, int negate, const void* A,
                          int lda, const void* B, int ldb, int beta, const void* C, int ldc, void* D, int ldd) {
